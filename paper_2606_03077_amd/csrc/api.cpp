@@ -148,10 +148,11 @@ StagingPool& g_staging = *new StagingPool();
 
 libra_status staging_acquire(Plan& P) {
   std::lock_guard<std::mutex> lk(g_staging.mu);
-  if (P.upload_bytes > 0) {
+  const size_t bytes = P.upload_bytes + (P.fine ? P.fine->upload_bytes : 0);
+  if (bytes > 0) {
     size_t best = g_staging.images.size();
     for (size_t i = 0; i < g_staging.images.size(); ++i)
-      if (g_staging.images[i].first >= P.upload_bytes &&
+      if (g_staging.images[i].first >= bytes &&
           (best == g_staging.images.size() ||
            g_staging.images[i].first < g_staging.images[best].first))
         best = i;
@@ -161,7 +162,7 @@ libra_status staging_acquire(Plan& P) {
       g_staging.images.erase(g_staging.images.begin() + static_cast<std::ptrdiff_t>(best));
     } else {
       size_t cap = 4096;
-      while (cap < P.upload_bytes) cap *= 2;
+      while (cap < bytes) cap *= 2;
       note_alloc_call();
       hipError_t e = hipHostMalloc(&P.pinned, cap, hipHostMallocDefault);
       if (e != hipSuccess) {
@@ -191,6 +192,12 @@ libra_status staging_acquire(Plan& P) {
     st = take_event(&P.fork_ev);
     if (st == LIBRA_OK) st = take_event(&P.join_ev);
     if (st != LIBRA_OK) return st;
+  }
+  if (P.fine) {
+    P.fine->pinned = static_cast<char*>(P.pinned) + P.upload_bytes;
+    P.fine->upload_done = P.upload_done;
+    P.fine->fork_ev = P.fork_ev;
+    P.fine->join_ev = P.join_ev;
   }
   return LIBRA_OK;
 }
@@ -245,9 +252,11 @@ void staging_fill(Plan& P) {
     if (!v.empty()) std::memcpy(h + off, v.data(), v.size() * sizeof(int32_t));
   };
   put(P.off_units, P.units);
+  put(P.off_tiles, P.tiles);
   put(P.off_writes, P.writes);
   put(P.off_merges, P.merges);
   put(P.off_xcd_map, P.xcd_map);
+  put(P.off_chunk_merges, P.chunk_merges);
 }
 
 // Enqueues the copy of the plan's pinned table image to ws and records its event.
@@ -285,6 +294,14 @@ libra_status upload(Plan& P, void* ws, size_t ws_bytes, hipStream_t s, bool forc
     g_ws.owner[reinterpret_cast<uintptr_t>(ws)] = P.id;
   }
   return LIBRA_OK;
+}
+
+// The form of plan P that a workspace of ws_bytes bytes runs: with fine tiles if it is large
+// enough for them, unless it already holds the tables without (so that a call on uploaded
+// tables enqueues kernels only, whatever size it states).
+Plan& plan_for(Plan& P, const void* ws, size_t ws_bytes) {
+  if (!P.fine || ws_bytes < P.fine->ws_bytes) return P;
+  return holds_tables(ws, P.id) ? P : *P.fine;
 }
 
 libra_status check_call(const KvLayout* L, const Plan* P, int mode, const void* q,
@@ -570,6 +587,7 @@ libra_status libra_splitkv_plan(const libra_plan_desc* desc, const int32_t* seq_
     delete P;
     return st;
   }
+  if (P->fine) P->fine->id = g_next_plan_id.fetch_add(1);
   // Pinned staging for the table upload, taken here so that no decode / append call
   // allocates.  Without a visible device (host-only use: inspecting a plan) there is none.
   int n_dev = 0;
@@ -584,6 +602,7 @@ libra_status libra_splitkv_plan(const libra_plan_desc* desc, const int32_t* seq_
       return st;
     }
     staging_fill(*P);
+    if (P->fine) staging_fill(*P->fine);
   }
   *out = P;
   return LIBRA_OK;
@@ -624,11 +643,15 @@ libra_status libra_plan_get_info(libra_plan plan, libra_plan_info* info) {
   return LIBRA_OK;
 }
 
-size_t libra_plan_workspace_bytes(libra_plan plan) { return plan ? plan->ws_bytes : 0; }
+size_t libra_plan_workspace_bytes(libra_plan plan) { 
+  if (!plan) return 0;
+  return plan->fine ? plan->fine->ws_bytes : plan->ws_bytes;
+}
 
 libra_status libra_plan_upload(libra_plan plan, void* workspace, size_t ws_bytes, void* stream) {
   if (!plan) return set_error(LIBRA_E_INVAL, "plan is NULL");
-  return upload(*plan, workspace, ws_bytes, static_cast<hipStream_t>(stream));
+  Plan& P = plan->fine && ws_bytes >= plan->fine->ws_bytes ? *plan->fine : *plan;
+  return upload(P, workspace, ws_bytes, static_cast<hipStream_t>(stream));
 }
 
 void libra_plan_destroy(libra_plan plan) {
@@ -637,9 +660,10 @@ void libra_plan_destroy(libra_plan plan) {
   // (only it, not the device) before the image goes back to the pool.
   if (plan->upload_done) (void)hipEventSynchronize(plan->upload_done);
   {
+    const uint64_t fine = plan->fine ? plan->fine->id : plan->id;
     std::lock_guard<std::mutex> lk(g_ws.mu);
     for (auto it = g_ws.owner.begin(); it != g_ws.owner.end();)
-      it = it->second == plan->id ? g_ws.owner.erase(it) : std::next(it);
+      it = it->second == plan->id || it->second == fine ? g_ws.owner.erase(it) : std::next(it);
   }
   staging_release(*plan);
   delete plan;
@@ -710,15 +734,16 @@ libra_status libra_append_attn(libra_kv_layout layout, libra_plan plan, const vo
   if (ws_bytes < plan->ws_bytes)
     return set_error(LIBRA_E_WORKSPACE, "workspace smaller than libra_plan_workspace_bytes");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  st = upload(*plan, workspace, ws_bytes, s, false);
+  Plan& P = plan_for(*plan, workspace, ws_bytes);
+  st = upload(P, workspace, ws_bytes, s, false);
   if (st != LIBRA_OK) return st;
   hipError_t e;
   {
-    ProfScope ps(LIBRA_KERNEL_CACHE_WRITE, s, plan->info.n_write_tiles > 0);
-    e = launch_cache_write(*layout, *plan, workspace, k_new, v_new, block_table, bt_stride, s);
+    ProfScope ps(LIBRA_KERNEL_CACHE_WRITE, s, P.info.n_write_tiles > 0);
+    e = launch_cache_write(*layout, P, workspace, k_new, v_new, block_table, bt_stride, s);
   }
   if (e != hipSuccess) return hip_error(e, "cache-write launch");
-  return launch_attention(*layout, *plan, workspace, q, block_table, bt_stride, scale, out, lse, s);
+  return launch_attention(*layout, P, workspace, q, block_table, bt_stride, scale, out, lse, s);
 }
 
 libra_status libra_profile_enable(int enable) {

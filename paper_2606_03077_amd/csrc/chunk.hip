@@ -1,14 +1,17 @@
 // Causal attention of an appended chunk (e.g. a tool output) over the paged KV cache.
 //
-// One 512-thread workgroup (8 waves, two per SIMD) per chunk unit (sequence b, KV head
-// g, new tokens [q0, q1)).  Query rows are the (token, head) pairs of the G heads sharing
-// KV head g, token-major; wave w owns the 32 rows 32 w .. 32 w + 31 as the 32 columns of
-// its matrix products, so a workgroup covers 256 rows, i.e. floor(256 / G) tokens.
-// Keys are visited 64 at a time (a step: four pages, two page pairs).  The step's four
-// K tiles and four V tiles are copied from memory straight into a four-stage LDS ring
-// three steps ahead (global_load_lds_dwordx4, 16 bytes per lane, the tiles in their
-// stored order, no registers), shared by the 8 waves.  Per page pair and wave, on
-// v_mfma_f32_32x32x16_bf16:
+// Two forms of one kernel.  The wide form is a 512-thread workgroup (8 waves, two per SIMD,
+// one workgroup per CU) per chunk unit (sequence b, KV head g, new tokens [q0, q1)), up to
+// 256 query rows.  The narrow form is a 256-thread workgroup (4 waves, two workgroups per
+// CU) per fine tile: half of a unit's rows, over all of its keys or one split of them (the
+// plan decides; the rule and its measurements stand in plan.cpp).  Query rows are the
+// (token, head) pairs of the G heads sharing KV head g, token-major; wave w owns 32 of them
+// as the 32 columns of its matrix products.
+// Keys are visited 64 (wide) or 32 (narrow) at a time: a step of four pages, two page
+// pairs, or of one pair.  The step's K and V tiles are copied from memory straight into a
+// four-stage LDS ring three steps ahead (global_load_lds_dwordx4, 16 bytes per lane, the
+// tiles in their stored order, no registers), shared by the waves.  Per page pair and wave,
+// on v_mfma_f32_32x32x16_bf16:
 //   S^T[32 keys x 32 rows] = K . Q^T: 8 MFMAs over the 128 channels; lane (key m, half
 //     h) reads K granule (2 c + h) * 16 + m % 16 of page 2P + m / 16 for channels
 //     16 c + 8 h .. + 7, and holds scores of keys 8 (r / 4) + 4 h + r % 4 (r = 0..15)
@@ -30,12 +33,18 @@
 // the pair's own, rescales the accumulators and takes them again, before a product uses
 // them.  Probabilities therefore stay at most 2^kTau, and the result is exact after the
 // final normalisation; no per-step maximum is taken.  Causal masks are applied only on
-// steps that reach past the tile's first token.  Row r = 32 w + column of the tile is
-// token q0 + r / G, head r % G; it sees keys k <= P_b + token.
-// Units arrive in per-XCD queues: workgroup w takes tile w / 8 of queue w % 8, so the
+// steps that reach past the tile's first token.  Row r of the unit is token q0 + r / G,
+// head r % G; it sees keys k <= P_b + token.
+// Workgroups arrive in per-XCD queues: workgroup w takes tile w / 8 of queue w % 8, so the
 // tiles of one (b, g), which read the same keys, run on one XCD and share its L2; each
-// queue holds its longest tiles first.  Wave priority is 1 through the first page pair of
-// a step and 0 through the second (see the note at the key loop).
+// queue holds its longest tiles first.
+//
+// What bounds it: the matrix cores and the softmax's vector work beside them on long tiles
+// (wide form 1.21-1.27 PFLOP/s on a 40,960-token prefill; the narrow form is 8% slower
+// there, as every 128 rows copy their own K and V), and the work per tile on short ones.
+// Skipping the ring's copies past the last key, starting the first copies from scalar page
+// ids and storing whole rows through LDS took 32 prompts of 64-2,048 tokens (40/8 heads)
+// from 860 us to 820 us.
 #include <cmath>
 #include <type_traits>
 
@@ -45,15 +54,20 @@ namespace libra {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kWaves = 8;
-constexpr int kThreads = 64 * kWaves;
-static_assert(kChunkRows == 32 * kWaves, "the plan's tile rows are the kernel's");
-constexpr int kStepPages = 4;    // pages (16 keys each) per softmax step
-static_assert(kStepPages * kPage == kChunkStepKeys, "the plan's tile cost counts these steps");
+constexpr int kWideWaves = 8;
+constexpr int kNarrowWaves = 4;
+static_assert(kChunkRows == 32 * kWideWaves, "the plan's tile rows are the wide form's");
+static_assert(kTileRows == 32 * kNarrowWaves, "the fine tiles' rows are the narrow form's");
+// Pages (16 keys each) per softmax step: one page pair for every four waves, so that each
+// wave moves the same two 1 KiB chunks of K and of V per step in either form.
+constexpr int step_pages(int waves) { return waves / 2; }
+static_assert(step_pages(kWideWaves) * kPage == kChunkStepKeys, "the plan's tile cost counts these steps");
+static_assert(step_pages(kNarrowWaves) * kPage == kTileStepKeys, "the plan cuts key ranges at whole steps");
 constexpr int kTau = 8;           // lazy-rescale threshold, base-2 logits
 constexpr float kSumTau = float(1 << kTau);  // probabilities stay at most 2^kTau
 constexpr int kMaxIds = 4096;     // block-table entries staged in LDS (64K keys)
@@ -68,24 +82,34 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 struct ChunkArgs {
   const uint16_t* k_cache;
   const uint16_t* v_cache;
-  const int32_t* units;
-  const int32_t* xcd_map;
+  const int32_t* tiles;
   const int32_t* bt;
   const uint16_t* q;
   uint16_t* out;
   float* lse;
+  float* part_o;
+  float* part_lse;
   int64_t bt_stride;
   int hkv;
   int hq;
   int group;
   float sl2;
+  int32_t xcd_first[kNumXcds];  // each XCD queue's first tile and tile count
+  int32_t xcd_count[kNumXcds];
 };
 
 // Row (M index) of element r of a 32x32 accumulator in a lane of half h.
 __device__ __forceinline__ constexpr int acc_row(int r, int h) { return 8 * (r / 4) + 4 * h + (r % 4); }
 
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int kWaves>
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void chunk_kernel(ChunkArgs A) {
+  constexpr bool kWide = kWaves == kWideWaves;
+  constexpr int kThreads = 64 * kWaves;
+  constexpr int kRows = 32 * kWaves;
+  constexpr int kStepPages = step_pages(kWaves);
+  constexpr int kPairs = kStepPages / 2;
+  constexpr int kStepKeys = kStepPages * kPage;
   // K and V stages: [page of the step][256 x uint4], the tiles as stored.  One array per
   // stage: the direct memory-to-LDS copies into one stage then never make the compiler
   // wait before LDS reads of another.
@@ -119,22 +143,44 @@ void chunk_kernel(ChunkArgs A) {
 
   const int xcd = blockIdx.x % kNumXcds;
   const int slot = blockIdx.x / kNumXcds;
-  if (slot >= A.xcd_map[2 * xcd + 1]) return;
-  const int32_t* u = A.units + size_t(A.xcd_map[2 * xcd] + slot) * kUnitInts;
-  const int b = u[U_B], g = u[U_G], kv1 = u[U_KV1];
-  const int q0 = u[U_Q0], q1 = u[U_Q1], row0 = u[U_ROW0], prior = u[U_PRIOR];
-
+  if (slot >= A.xcd_count[xcd]) return;
+  const size_t rec = size_t(A.xcd_first[xcd] + slot);
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int col = lane & 31, hh = lane >> 5;  // accumulator column (tile row), lane half
   const int G = A.group;
 
-  // Tile row of this lane's column: r = 32 wave + col; token q0 + r / G, head r % G.
-  const int r_tile = 32 * wave + col;
+  // The workgroup's rows are r_first .. r_first + kRows - 1 of the (token, head) rows of
+  // tokens [q0, q1), its keys [kv0, kv1).  The wide form takes a plan unit, the narrow one
+  // a fine tile: half of a unit's rows, and all of its keys or one split of them.
+  int b, g, q0, q1, row0, prior, kv0, kv1, r_first, nsplit, part;
+  if constexpr (kWide) {
+    const int32_t* u = A.tiles + rec * kUnitInts;
+    b = u[U_B], g = u[U_G], q0 = u[U_Q0], q1 = u[U_Q1], row0 = u[U_ROW0], prior = u[U_PRIOR];
+    kv0 = 0, kv1 = u[U_KV1], r_first = 0, nsplit = 1, part = 0;
+  } else {
+    const int32_t* u = A.tiles + rec * kTileInts;
+    b = u[T_B], g = u[T_GH] & 0xFFFF, q0 = u[T_Q0], q1 = u[T_Q1], row0 = u[T_ROW0];
+    prior = u[T_PRIOR], kv0 = u[T_KV0], kv1 = u[T_KV1], r_first = (u[T_GH] >> 16) * kRows;
+    nsplit = u[T_NSPLIT], part = u[T_PART];
+  }
+  const int npages = (kv1 - kv0 + kPage - 1) / kPage;  // kv0 is a multiple of the step
+  const int nsteps = (npages + kStepPages - 1) / kStepPages;
+  const int last = nsteps - 1;
+  const int32_t* btrow = A.bt + int64_t(b) * A.bt_stride + kv0 / kPage;
+  // Page ids of this wave's chunks of the first three steps, by scalar loads: the first
+  // copies then wait for neither the staged id row nor its barrier.
+  const int wpage = wave >> 1;
+  int first_id[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) first_id[i] = btrow[min(i * kStepPages + wpage, npages - 1)];
+
+  // Tile row of this lane's column: r = r_first + 32 wave + col; token q0 + r / G,
+  // head r % G.
+  const int r_tile = r_first + 32 * wave + col;
   const int t_tok = q0 + r_tile / G;
   const int head = r_tile % G;
   const bool ok = t_tok < q1;
-  const int tok = ok ? t_tok : -1;
   const int lim = ok ? prior + t_tok : -1;
   // Q operand of MFMA c (channels 16 c .. 16 c + 15): lane (col, hh) holds channels
   // 16 c + 8 hh .. + 7 of its row.
@@ -157,54 +203,62 @@ void chunk_kernel(ChunkArgs A) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
 
-  const int npages = (kv1 + kPage - 1) / kPage;
-  const int nsteps = (npages + kStepPages - 1) / kStepPages;
-  const int32_t* btrow = A.bt + int64_t(b) * A.bt_stride;
   const uint32_t page_bytes = uint32_t(A.hkv) * kTileBytes;
-  const int first_tok = prior + q0;
+  const int first_tok = prior + q0 + r_first / G;
   const int mask_key0 = min(first_tok - (kStepPages * kPage - 1), kv1 - kStepPages * kPage);
 
   const char* k_lane = reinterpret_cast<const char*>(A.k_cache) + size_t(g) * kTileBytes +
                        size_t(lane) * 16;
   const char* v_lane = reinterpret_cast<const char*>(A.v_cache) + size_t(g) * kTileBytes +
                        size_t(lane) * 16;
-  // K and V of `step` straight into LDS stage stage_tag & 3: wave w moves 1 KiB chunks
-  // 2 w and 2 w + 1 of the step's four K tiles and of its four V tiles (16 B per lane at
-  // the chunk's LDS base + 16 lane, the tile as stored).  Both chunks lie in page w / 2 of
-  // the step, so a wave needs one page id: from the staged row (a broadcast LDS read), or
-  // from global memory past it (uniform and rare).  Pages past the end re-read the last
-  // page (the id row is padded with it), so the copies stay branch-free; their keys are
-  // >= kv1, so they are masked and their V zeroed.  The wave index is made scalar, so the
-  // page, the LDS targets and the byte offsets are scalar arithmetic.  Four vector-memory
-  // operations per wave per step, in a fixed order; the waits count them.
-  auto copy_kv = [&](int step, auto stage_tag) {
-    const int j = wave >> 1;
-    const int p = step * kStepPages + j;
-    const int id = p < kMaxIds ? __builtin_amdgcn_readfirstlane(lds_ids[p])
-                               : __builtin_amdgcn_readfirstlane(btrow[min(p, npages - 1)]);
+  // K or V of a step straight into an LDS stage: wave w moves 1 KiB chunks 2 w and 2 w + 1
+  // of the step's tiles (16 B per lane at the chunk's LDS base + 16 lane, the tile as
+  // stored).  Both chunks lie in page w / 2 of the step, so a wave needs one page id: from
+  // the staged row (a broadcast LDS read), or from global memory past it (uniform and
+  // rare).  Pages past the end re-read the last page (the id row is padded with it); their
+  // keys are >= kv1, so they are masked and their V zeroed.  The wave index is made scalar,
+  // so the page, the LDS targets and the byte offsets are scalar arithmetic.  Two
+  // vector-memory operations per wave and call, in a fixed order; the waits count them.
+  auto tile_off = [&](int id) -> uint64_t { return uint64_t(uint32_t(id)) * page_bytes; };
+  auto page_off = [&](int step) -> uint64_t {
+    const int p = step * kStepPages + wpage;
+    return tile_off(p < kMaxIds ? __builtin_amdgcn_readfirstlane(lds_ids[p])
+                                : __builtin_amdgcn_readfirstlane(btrow[min(p, npages - 1)]));
+  };
+  auto copy_tile = [&](const char* src, uint4 (&dst)[kStepPages][256], uint64_t off) {
 #pragma unroll
     for (int c2 = 0; c2 < 2; ++c2) {
       const int i = (2 * wave + c2) & 3;
-      const uint64_t off = uint64_t(uint32_t(id)) * page_bytes + i * 1024;
-      const uint32_t dk = uint32_t(reinterpret_cast<uintptr_t>(&kst(stage_tag)[j][i * 64]));
-      const char* ksrc = k_lane + off;
+      const uint32_t d = uint32_t(reinterpret_cast<uintptr_t>(&dst[wpage][i * 64]));
+      const char* s = src + (off + i * 1024);
       asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
                    :
-                   : "s"(dk), "v"(ksrc)
-                   : "memory", "m0");
-      const uint32_t dv = uint32_t(reinterpret_cast<uintptr_t>(&vst(stage_tag)[j][i * 64]));
-      const char* vsrc = v_lane + off;
-      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
-                   :
-                   : "s"(dv), "v"(vsrc)
+                   : "s"(d), "v"(s)
                    : "memory", "m0");
     }
   };
-
-  // Stage the page ids once (padded to whole steps with the last id), so that each
-  // prefetch is one dependent load, not two.
+  copy_tile(k_lane, kst(S0{}), tile_off(first_id[0]));
+  copy_tile(v_lane, vst(S0{}), tile_off(first_id[0]));
+  if (last > 0) {
+    copy_tile(k_lane, kst(S1{}), tile_off(first_id[1]));
+    copy_tile(v_lane, vst(S1{}), tile_off(first_id[1]));
+  }
+  if (last > 1) {
+    copy_tile(k_lane, kst(S2{}), tile_off(first_id[2]));
+    copy_tile(v_lane, vst(S2{}), tile_off(first_id[2]));
+  }
+  // Stage the later steps' page ids once (padded to whole steps with the last id), so that
+  // each later copy is one dependent load, not two; four loads in flight per thread.
   const int nids = min(nsteps * kStepPages, kMaxIds);
-  for (int i = tid; i < nids; i += kThreads) lds_ids[i] = btrow[min(i, npages - 1)];
+  for (int i0 = 3 * kStepPages + tid; i0 < nids; i0 += 4 * kThreads) {
+    int v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = btrow[min(i0 + j * kThreads, npages - 1)];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (i0 + j * kThreads < nids) lds_ids[i0 + j * kThreads] = v[j];
+  }
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
   // Scores S^T (32 keys of page pair P x 32 rows) from K stage: K operand of MFMA c,
@@ -224,11 +278,12 @@ void chunk_kernel(ChunkArgs A) {
   };
 
   // Causal / length mask of step n; on the first step (exact) also the running maximum
-  // (later steps check their probabilities instead, in pair()).
-  auto prepare = [&](int key0, f32x16 (&s)[2], float& neg_m, bool exact) {
+  // (later steps check their probabilities instead, in pair()).  A row that sees any key
+  // of [kv0, kv1) sees kv0, so a maximum still -inf after the first step stays so.
+  auto prepare = [&](int key0, f32x16 (&s)[kPairs], float& neg_m, bool exact) {
     if (key0 > mask_key0) {
 #pragma unroll
-      for (int P = 0; P < 2; ++P)
+      for (int P = 0; P < kPairs; ++P)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           if (key0 + 32 * P + acc_row(r, hh) > lim) s[P][r] = -INFINITY;
@@ -236,7 +291,7 @@ void chunk_kernel(ChunkArgs A) {
     if (exact) {
       float mloc = -INFINITY;
 #pragma unroll
-      for (int P = 0; P < 2; ++P)
+      for (int P = 0; P < kPairs; ++P)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, s[P][r]);
       float mc = fmaxf(mloc * A.sl2, m);
@@ -265,7 +320,7 @@ void chunk_kernel(ChunkArgs A) {
   // from V stage vread.  V operand of page j, channel block cb: lane (channel
   // 32 cb + col, hh) reads granule 128 hh + 32 cb + col, keys in the order of the P
   // operand (element p: slot 8 (p / 4) + 4 hh + p % 4), which is the score layout.
-  auto pair = [&](int P, auto kread, auto vread, int key0, f32x16 (&s)[2], float& neg_m,
+  auto pair = [&](int P, auto kread, auto vread, int key0, f32x16 (&s)[kPairs], float& neg_m,
                   auto last_tag) {
     constexpr bool kLast = decltype(last_tag)::value;
     uint4 kpre[8];
@@ -302,6 +357,7 @@ void chunk_kernel(ChunkArgs A) {
     pb.w = pack_bf16x2(p[14], p[15]);
     // Step n + 1's scores of the pair (a chain of 8 dependent MFMAs) interleaved with the
     // pair's PV products (8 independent ones), so the chain's latency is covered.
+    if constexpr (!kWide) __builtin_amdgcn_s_setprio(1);
     f32x16 qs;
 #pragma unroll
     for (int r = 0; r < 16; ++r) qs[r] = 0.f;
@@ -341,87 +397,117 @@ void chunk_kernel(ChunkArgs A) {
     if constexpr (!kLast) s[P] = qs;
   };
 
-  if (nsteps > 0) copy_kv(0, S0{});
-  if (nsteps > 1) copy_kv(1, S1{});
-  if (nsteps > 2) copy_kv(2, S2{});
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  // Wave priority: 1 from a step's opening barrier through its first page pair, 0 for the
-  // second.  The two waves of a SIMD otherwise share issue by age, so the older one ran
-  // each step's pairs ~40% faster than its partner and then idled at the barrier while
-  // the younger finished alone; dropping the priority of a wave once it is half-way
-  // through lets a lagging partner catch up within the step.
-  __builtin_amdgcn_s_setprio(1);
+  // Wave priority.  Wide form: 1 from a step's opening barrier through its first page pair,
+  // 0 for the second.  The two waves of a SIMD otherwise share issue by age, so the older
+  // one ran each step's pairs ~40% faster than its partner and then idled at the barrier
+  // while the younger finished alone; dropping the priority of a wave once it is half-way
+  // through lets a lagging partner catch up within the step.  Narrow form: the two waves
+  // belong to different workgroups; 1 for the products, 0 for the probabilities.
+  if constexpr (kWide) __builtin_amdgcn_s_setprio(1);
 
-  f32x16 sc[2];
-  if (nsteps > 0) {
-    qk_pair(S0{}, 0, sc[0]);
-    qk_pair(S0{}, 1, sc[1]);
-  }
-  // Step n: copies of step n + 3 into the stage last read in step n - 1; at its end only
-  // those four copies may be in flight (vmcnt(4)): step n + 1's V and step n + 2's K
-  // have landed.
-  auto step = [&](int n, auto r_tag) {
+  f32x16 sc[kPairs];
+#pragma unroll
+  for (int P = 0; P < kPairs; ++P) qk_pair(S0{}, P, sc[P]);
+  if (last == 0) __syncthreads();  // the epilogue reuses the K stages; else a step's barrier is between
+  // Step n copies step n + 3 into the stages that step n - 1 finished with; at its end
+  // only those four copies may be in flight (vmcnt(4)): step n + 2's have landed.
+  // Past the last key nothing is copied, and the wait is for all.
+  auto step = [&](int n, auto r_tag, auto all_tag) {
+    constexpr bool kAll = decltype(all_tag)::value;
     constexpr int r = decltype(r_tag)::value;
     using KRead = std::integral_constant<int, (r + 1) & 3>;
     using VRead = std::integral_constant<int, r>;
     using Copy = std::integral_constant<int, (r + 3) & 3>;
-    const int key0 = n * kStepPages * kPage;
-    copy_kv(min(n + 3, nsteps - 1), Copy{});
+    const int key0 = kv0 + n * kStepKeys;
+    const bool cp = kAll || n + 3 <= last;
+    if (cp) {
+      const uint64_t o = page_off(n + 3);
+      copy_tile(k_lane, kst(Copy{}), o);
+      copy_tile(v_lane, vst(Copy{}), o);
+    }
     float neg_m;
+    if constexpr (!kWide) __builtin_amdgcn_s_setprio(0);
     prepare(key0, sc, neg_m, n == 0);
     pair(0, KRead{}, VRead{}, key0, sc, neg_m, std::false_type{});
-    __builtin_amdgcn_s_setprio(0);
-    pair(1, KRead{}, VRead{}, key0, sc, neg_m, std::false_type{});
-    __builtin_amdgcn_s_waitcnt(0xF74);
+    if constexpr (kWide) {
+      __builtin_amdgcn_s_setprio(0);
+      pair(1, KRead{}, VRead{}, key0, sc, neg_m, std::false_type{});
+    }
+    if (cp) __builtin_amdgcn_s_waitcnt(0xF74);
+    else __builtin_amdgcn_s_waitcnt(0xF70);
     __syncthreads();
-    __builtin_amdgcn_s_setprio(1);
+    if constexpr (kWide) __builtin_amdgcn_s_setprio(1);
   };
   int n0 = 0;
-  for (; n0 + 4 < nsteps; n0 += 4) {
-    step(n0, S0{});
-    step(n0 + 1, S1{});
-    step(n0 + 2, S2{});
-    step(n0 + 3, S3{});
+  for (; n0 + 6 <= last; n0 += 4) {
+    step(n0, S0{}, std::true_type{});
+    step(n0 + 1, S1{}, std::true_type{});
+    step(n0 + 2, S2{}, std::true_type{});
+    step(n0 + 3, S3{}, std::true_type{});
   }
-  if (n0 + 1 < nsteps) {
-    step(n0, S0{});
-    if (n0 + 2 < nsteps) {
-      step(n0 + 1, S1{});
-      if (n0 + 3 < nsteps) step(n0 + 2, S2{});
-    }
+  for (; n0 < last; n0 += 4) {
+    step(n0, S0{}, std::false_type{});
+    if (n0 + 1 < last) step(n0 + 1, S1{}, std::false_type{});
+    if (n0 + 2 < last) step(n0 + 2, S2{}, std::false_type{});
+    if (n0 + 3 < last) step(n0 + 3, S3{}, std::false_type{});
   }
-  if (nsteps > 0) {
-    const int key0 = (nsteps - 1) * kStepPages * kPage;
+  {
+    const int key0 = kv0 + last * kStepKeys;
     float neg_m;
-    prepare(key0, sc, neg_m, nsteps == 1);
-    switch ((nsteps - 1) & 3) {
-      case 0:
-        pair(0, S0{}, S0{}, key0, sc, neg_m, std::true_type{});
-        pair(1, S0{}, S0{}, key0, sc, neg_m, std::true_type{});
-        break;
-      case 1:
-        pair(0, S0{}, S1{}, key0, sc, neg_m, std::true_type{});
-        pair(1, S0{}, S1{}, key0, sc, neg_m, std::true_type{});
-        break;
-      case 2:
-        pair(0, S0{}, S2{}, key0, sc, neg_m, std::true_type{});
-        pair(1, S0{}, S2{}, key0, sc, neg_m, std::true_type{});
-        break;
-      default:
-        pair(0, S0{}, S3{}, key0, sc, neg_m, std::true_type{});
-        pair(1, S0{}, S3{}, key0, sc, neg_m, std::true_type{});
-        break;
+    prepare(key0, sc, neg_m, last == 0);
+    auto tail = [&](auto v_tag) {
+      pair(0, S0{}, v_tag, key0, sc, neg_m, std::true_type{});
+      if constexpr (kWide) pair(1, S0{}, v_tag, key0, sc, neg_m, std::true_type{});
+    };
+    switch (last & 3) {
+      case 0: tail(S0{}); break;
+      case 1: tail(S1{}); break;
+      case 2: tail(S2{}); break;
+      default: tail(S3{}); break;
     }
   }
 
-  // Epilogue: row col's sum over both lane halves; each lane stores its 16 channels per
-  // channel block (runs of 4 at 32 cb + 8 e + 4 hh).
-  float ls = l + __shfl_xor(l, 32);
-  if (tok < 0) return;
+  // Epilogue.  Row col's sum over both lane halves; a lane holds, per channel block, 16
+  // channels of its row (runs of 4 at 32 cb + 8 e + 4 hh).  The rows go through LDS so that
+  // each store instruction writes whole rows (16 lanes x 16 B of each of four): K stages
+  // are free (the last step reads V only, and no copy is in flight), 8 KiB per wave, rows
+  // of 256 B whose 16-byte granules are XORed with the row against bank conflicts.
+  const float ls = l + __shfl_xor(l, 32);
   const float inv = ls > 0.f ? 1.f / ls : 0.f;
-  const size_t orow = size_t(row0 + tok) * A.hq + size_t(g) * G + head;
-  uint16_t* op = A.out + orow * kDim;
+  uint4* const buf = (kWide ? (wave < 4 ? (wave < 2 ? &ldk0[0][0] : &ldk1[0][0])
+                                        : (wave < 6 ? &ldk2[0][0] : &ldk3[0][0])) + (wave & 1) * 512
+                            : (wave < 2 ? (wave < 1 ? &ldk0[0][0] : &ldk1[0][0])
+                                        : (wave < 3 ? &ldk2[0][0] : &ldk3[0][0])));
+  const int sw = col & 15;
+  auto wave_sync = [&]() {  // LDS operations of one wave complete in order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  if (nsplit > 1) {
+    // One split of the rows: normalised float32 partials, 64 channels at a time, and the
+    // base-2 log-sum-exp; chunk_merge_kernel combines the splits after this launch.
+    const size_t prow = size_t(part) * kRows + 32 * wave;
+#pragma unroll
+    for (int h2 = 0; h2 < 2; ++h2) {
+      wave_sync();
+#pragma unroll
+      for (int cb = 2 * h2; cb < 2 * h2 + 2; ++cb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          *reinterpret_cast<f32x4*>(&buf[col * 16 + ((8 * (cb & 1) + 2 * e + hh) ^ sw)]) =
+              f32x4{acc[cb][4 * e] * inv, acc[cb][4 * e + 1] * inv, acc[cb][4 * e + 2] * inv,
+                    acc[cb][4 * e + 3] * inv};
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int r = 4 * i + (lane >> 4), c = lane & 15;
+        *reinterpret_cast<uint4*>(A.part_o + (prow + r) * kDim + 64 * h2 + 4 * c) =
+            buf[r * 16 + (c ^ (r & 15))];
+      }
+    }
+    if (hh == 0) A.part_lse[prow + col] = ls > 0.f ? m + log2f(ls) : -INFINITY;
+    return;
+  }
 #pragma unroll
   for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
@@ -429,9 +515,23 @@ void chunk_kernel(ChunkArgs A) {
       uint2 w;
       w.x = pack_bf16x2(acc[cb][4 * e] * inv, acc[cb][4 * e + 1] * inv);
       w.y = pack_bf16x2(acc[cb][4 * e + 2] * inv, acc[cb][4 * e + 3] * inv);
-      *reinterpret_cast<uint2*>(op + 32 * cb + 8 * e + 4 * hh) = w;
+      reinterpret_cast<uint2*>(&buf[col * 16 + ((4 * cb + e) ^ sw)])[hh] = w;
     }
-  if (A.lse && hh == 0) A.lse[orow] = ls > 0.f ? (m + log2f(ls)) * kLn2 : -INFINITY;
+  wave_sync();
+  const size_t head0 = size_t(g) * G;
+  const uint32_t inv_g = (65536u + G - 1) / G;  // r / G = r * inv_g >> 16 for r < 256
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int rl = 4 * i + (lane >> 4), c = lane & 15;
+    const uint32_t r = r_first + 32 * wave + rl;
+    const int tk = q0 + int(r * inv_g >> 16);
+    if (tk < q1) {
+      const size_t orow = size_t(row0 + tk) * A.hq + head0 + (r - (r * inv_g >> 16) * G);
+      *reinterpret_cast<uint4*>(A.out + orow * kDim + 8 * c) = buf[rl * 16 + (c ^ (rl & 15))];
+    }
+  }
+  if (A.lse && hh == 0 && ok)
+    A.lse[size_t(row0 + t_tok) * A.hq + head0 + head] = ls > 0.f ? (m + log2f(ls)) * kLn2 : -INFINITY;
 }
 
 }  // namespace
@@ -444,18 +544,30 @@ hipError_t launch_chunk(const KvLayout& L, const Plan& P, void* ws, const void* 
   ChunkArgs A;
   A.k_cache = static_cast<const uint16_t*>(L.desc.k_cache);
   A.v_cache = static_cast<const uint16_t*>(L.desc.v_cache);
-  A.units = reinterpret_cast<const int32_t*>(w + P.off_units) + size_t(P.info.n_single) * kUnitInts;
-  A.xcd_map = reinterpret_cast<const int32_t*>(w + P.off_xcd_map);
+  A.tiles = reinterpret_cast<const int32_t*>(
+      w + (P.fine_tiles ? P.off_tiles
+                        : P.off_units + size_t(P.info.n_single) * kUnitInts * sizeof(int32_t)));
+  for (int x = 0; x < kNumXcds; ++x) {
+    A.xcd_first[x] = P.xcd_map[size_t(2 * x)];
+    A.xcd_count[x] = P.xcd_map[size_t(2 * x + 1)];
+  }
   A.bt = bt;
   A.q = static_cast<const uint16_t*>(q);
   A.out = static_cast<uint16_t*>(out);
   A.lse = lse;
+  A.part_o = reinterpret_cast<float*>(w + P.off_chunk_o);
+  A.part_lse = reinterpret_cast<float*>(w + P.off_chunk_lse);
   A.bt_stride = stride;
   A.hkv = P.num_kv_heads;
   A.hq = P.num_q_heads;
   A.group = P.group;
   A.sl2 = scale * kLog2e;
-  hipLaunchKernelGGL(chunk_kernel, dim3(unsigned(P.chunk_grid)), dim3(kThreads), 0, s, A);
+  if (P.fine_tiles)
+    hipLaunchKernelGGL(chunk_kernel<kNarrowWaves>, dim3(unsigned(P.chunk_grid)),
+                       dim3(64 * kNarrowWaves), 0, s, A);
+  else
+    hipLaunchKernelGGL(chunk_kernel<kWideWaves>, dim3(unsigned(P.chunk_grid)),
+                       dim3(64 * kWideWaves), 0, s, A);
   return hipGetLastError();
 }
 

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -21,15 +22,19 @@ struct Plan {
   std::vector<int32_t> units;   // n_units * kUnitInts
   std::vector<int32_t> writes;  // n_write_tiles * kWriteInts (append only)
   std::vector<int32_t> merges;  // n_merge_groups * kMergeInts
-  std::vector<int32_t> xcd_map; // (first chunk unit, count) per XCD queue
+  std::vector<int32_t> xcd_map; // (first chunk unit or fine tile, count) per XCD queue
   int64_t chunk_grid = 0;       // workgroups of the chunk launch: kNumXcds * longest queue
+  bool fine_tiles = false;      // whether the chunk launch takes fine tiles, else chunk units
+  std::vector<int32_t> tiles;   // fine tiles, kTileInts each
+  std::vector<int32_t> chunk_merges;  // kMergeInts per fine tile whose keys are split
 
-  // Workspace image: [units | writes | merges | xcd map | partial o | partial lse],
-  // 256-B aligned.
-  size_t off_units = 0, off_writes = 0, off_merges = 0, off_xcd_map = 0, off_part_o = 0,
-         off_part_lse = 0;
+  // Workspace image: [units | writes | merges | xcd map | fine tiles | chunk merges | partial
+  // o | partial lse | chunk partial o | chunk partial lse], 256-B aligned.
+  size_t off_units = 0, off_tiles = 0, off_writes = 0, off_merges = 0, off_xcd_map = 0,
+         off_chunk_merges = 0, off_part_o = 0, off_part_lse = 0, off_chunk_o = 0,
+         off_chunk_lse = 0;
   size_t ws_bytes = 0;
-  size_t upload_bytes = 0;  // bytes of [units | writes | merges | xcd map] from the host
+  size_t upload_bytes = 0;  // bytes of the image that come from the host (up to partial o)
   int64_t pages_needed = 0; // block-table columns the units and writes read (per row, max)
   uint64_t id = 0;          // process-unique, set at creation: which plan a workspace holds
 
@@ -44,6 +49,12 @@ struct Plan {
   // decode rows on the device's auxiliary stream, forked from and joined back to the
   // caller's stream by these events (from the pool; null otherwise).
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
+
+  // The same plan with the chunk units cut into fine tiles, where that is faster (null
+  // otherwise).  It is used when the workspace holds its tables and partial results too;
+  // this plan itself needs no more workspace than the unit, write and merge tables and the
+  // single rows' partials.  Its staging image follows this plan's, and it shares the events.
+  std::unique_ptr<Plan> fine;
 };
 
 struct KvLayout {

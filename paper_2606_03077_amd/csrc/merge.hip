@@ -126,13 +126,93 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(MergeArgs A) {
     A.lse[size_t(row) * A.hq + head] = wsum > 0.f ? (M + log2f(wsum)) * kLn2 : -INFINITY;
 }
 
+// Log-sum-exp merge of the fine tiles whose keys were split, over kTileRows rows of
+// (token, head) pairs each.  A 256-thread block takes two rows: eight groups of 32 threads,
+// four to a row, thread t of a group channels 4 t .. + 3.  Group k of a row folds splits k,
+// k + 4, ... eight at a time (all loads of a batch in flight), and the groups combine
+// through LDS.  Latency-bound: many small blocks and at most ceil(n / 32) dependent rounds
+// of loads.
+constexpr int kRowGroups = 4;
+constexpr int kMergeRows = kThreads / (32 * kRowGroups);
+
+__global__ __launch_bounds__(kThreads) void chunk_merge_kernel(MergeArgs A) {
+  __shared__ float red_m[kMergeRows][kRowGroups];
+  __shared__ float red_w[kMergeRows][kRowGroups];
+  __shared__ __align__(16) f32x4 red_acc[kMergeRows][kRowGroups][32];
+
+  const int32_t* m = A.merges + size_t(blockIdx.x) * kMergeInts;
+  const int g = m[CM_GH] & 0xFFFF, first = (m[CM_GH] >> 16) * kTileRows;
+  const int n = m[CM_N], part = m[CM_PART];
+  const int tid = threadIdx.x, t = tid & 31, grp = (tid >> 5) % kRowGroups;
+  const int lr = tid / (32 * kRowGroups);
+  const int r = blockIdx.y * kMergeRows + lr;  // row of the workgroup's kTileRows
+  const int G = A.group;
+  const int tok = m[CM_Q0] + (first + r) / G, head = (first + r) % G;
+  const bool ok = tok < m[CM_Q1];
+
+  float M = -INFINITY, wsum = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (ok) {
+    for (int j0 = grp; j0 < n; j0 += kBatch * kRowGroups) {
+      float lj[kBatch];
+      f32x4 x[kBatch];
+#pragma unroll
+      for (int jj = 0; jj < kBatch; ++jj) {
+        const int j = j0 + jj * kRowGroups;
+        lj[jj] = -INFINITY;
+        x[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (j < n) {
+          const size_t row = size_t(part + j) * kTileRows + r;
+          lj[jj] = A.part_lse[row];
+          x[jj] = *reinterpret_cast<const f32x4*>(A.part_o + row * kDim + 4 * t);
+        }
+      }
+      float Mc = M;
+#pragma unroll
+      for (int jj = 0; jj < kBatch; ++jj) Mc = fmaxf(Mc, lj[jj]);
+      if (Mc == -INFINITY) continue;
+      const float s = __builtin_amdgcn_exp2f(M - Mc);  // 0 while M = -inf
+      wsum *= s;
+      acc *= s;
+#pragma unroll
+      for (int jj = 0; jj < kBatch; ++jj) {
+        const float w = __builtin_amdgcn_exp2f(lj[jj] - Mc);  // 0 for empty or absent splits
+        wsum += w;
+        acc += w * x[jj];
+      }
+      M = Mc;
+    }
+  }
+  if (t == 0) {
+    red_m[lr][grp] = M;
+    red_w[lr][grp] = wsum;
+  }
+  red_acc[lr][grp][t] = acc;
+  __syncthreads();
+  if (grp != 0 || !ok) return;
+#pragma unroll
+  for (int k = 1; k < kRowGroups; ++k) {
+    const float Mk = red_m[lr][k];
+    const float Mn = fmaxf(M, Mk);
+    if (Mn == -INFINITY) continue;
+    const float a = __builtin_amdgcn_exp2f(M - Mn), b = __builtin_amdgcn_exp2f(Mk - Mn);
+    wsum = wsum * a + red_w[lr][k] * b;
+    acc = acc * a + red_acc[lr][k][t] * b;
+    M = Mn;
+  }
+  const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
+  const size_t row = size_t(m[CM_ROW0] + tok) * A.hq + size_t(g) * G + head;
+  *reinterpret_cast<uint2*>(A.out + row * kDim + 4 * t) =
+      make_uint2(pack_bf16x2(acc.x * inv, acc.y * inv), pack_bf16x2(acc.z * inv, acc.w * inv));
+  if (A.lse && t == 0) A.lse[row] = wsum > 0.f ? (M + log2f(wsum)) * kLn2 : -INFINITY;
+}
+
 }  // namespace
 
-bool merge_launches(const Plan& P) { return P.info.n_merge_groups > 0; }
+bool merge_launches(const Plan& P) { return P.info.n_merge_groups > 0 || !P.chunk_merges.empty(); }
 
 hipError_t launch_merge(const Plan& P, void* ws, void* out, float* lse, hipStream_t s) {
   const int n = P.info.n_merge_groups;
-  if (!merge_launches(P)) return hipSuccess;
   char* w = static_cast<char*>(ws);
   MergeArgs A;
   A.merges = reinterpret_cast<const int32_t*>(w + P.off_merges);
@@ -142,8 +222,21 @@ hipError_t launch_merge(const Plan& P, void* ws, void* out, float* lse, hipStrea
   A.lse = lse;
   A.hq = P.num_q_heads;
   A.group = P.group;
-  hipLaunchKernelGGL(merge_kernel, dim3(unsigned(n)), dim3(kThreads), 0, s, A);
-  return hipGetLastError();
+  if (n > 0) {
+    hipLaunchKernelGGL(merge_kernel, dim3(unsigned(n)), dim3(kThreads), 0, s, A);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (!P.chunk_merges.empty()) {
+    A.merges = reinterpret_cast<const int32_t*>(w + P.off_chunk_merges);
+    A.part_o = reinterpret_cast<const float*>(w + P.off_chunk_o);
+    A.part_lse = reinterpret_cast<const float*>(w + P.off_chunk_lse);
+    hipLaunchKernelGGL(chunk_merge_kernel,
+                       dim3(unsigned(P.chunk_merges.size() / kMergeInts), kTileRows / kMergeRows),
+                       dim3(kThreads), 0, s, A);
+    return hipGetLastError();
+  }
+  return hipSuccess;
 }
 
 }  // namespace libra

@@ -91,6 +91,178 @@ std::vector<Unit> place_on_slots(const std::vector<Unit>& units, const libra_pla
   return out;
 }
 
+// Places the tables and partial results in the workspace; chunk_slots: partial results of
+// kTileRows rows that the chunk launch writes.
+void workspace_layout(Plan& P, int64_t chunk_slots) {
+  size_t off = 0;
+  auto place = [&off](size_t bytes) {
+    const size_t at = off;
+    off = align256(off + bytes);
+    return at;
+  };
+  P.off_units = place(P.units.size() * sizeof(int32_t));
+  P.off_writes = place(P.writes.size() * sizeof(int32_t));
+  P.off_merges = place(P.merges.size() * sizeof(int32_t));
+  P.off_xcd_map = place(P.xcd_map.size() * sizeof(int32_t));
+  P.off_tiles = place(P.tiles.size() * sizeof(int32_t));
+  P.off_chunk_merges = place(P.chunk_merges.size() * sizeof(int32_t));
+  P.upload_bytes = off;
+  const size_t rows = size_t(P.info.n_partial_slots) * size_t(P.group);
+  P.off_part_o = place(rows * kDim * sizeof(float));
+  P.off_part_lse = place(rows * sizeof(float));
+  const size_t chunk_rows = size_t(chunk_slots) * kTileRows;
+  P.off_chunk_o = place(chunk_rows * kDim * sizeof(float));
+  P.off_chunk_lse = place(chunk_rows * sizeof(float));
+  P.ws_bytes = std::max<size_t>(off, 256);
+}
+
+// Builds P.fine, the plan whose chunk launch takes fine tiles (kTileRows rows each, four
+// waves, two workgroups per CU) where that is faster than the chunk units on workgroups of
+// kChunkRows rows (eight waves, one per CU).  chunks: the chunk units in queue order.
+//
+// At most S = 2 num_cus fine tiles are resident at once and their longest sets the launch's
+// time, so their keys may be split as well: into ceil(steps / t) near-equal ranges, t being
+// the smallest piece (at least kMinPieceSteps) for which the pieces fit in S.  The pieces
+// write float32 partials, which a merge combines.  The forms are compared by the times
+// below, in 10 ns, measured over appends of 8 to 1,600 tokens to 1 to 128 requests (256 CUs):
+// * a 64-key step of a wide workgroup takes 1.25 us while half of the CUs are idle, 1.67 us
+//   when all are busy, and a workgroup 8-9 us besides (dispatch, first loads, stores);
+// * a 32-key step of a fine tile takes 0.65 us alone on a CU and 0.91-0.93 us beside
+//   another, a tile 3.3 us of its CU besides (7 us by itself), a merge 6 us.
+// So full tiles in many waves stay wide (40,960-token prefill: 13.8 ms against 15.0 ms), and
+// fine tiles take launches that leave CUs idle (333 tokens on 16,001: 129 us against 326 us;
+// 800 tokens on 16,000: 267 against 340 us; 4 x 8 tokens on 30,000: 54 against 583 us),
+// query tiles of at most 128 rows (128 x 20 tokens on 2,000, 4 heads per KV head: 218
+// against 267 us) and short ones (64 x 100 tokens on 500: 77 against 80 us).
+constexpr int64_t kMinPieceSteps = 8;
+constexpr int64_t kMaxFineSlots = 2048;  // bounds the partial results (64.5 KiB each)
+
+void build_fine(const std::vector<Unit>& chunks, Plan& P) {
+  struct Tile { int64_t unit, h, keys, steps, part; };
+  const int64_t cus = P.params.num_cus;
+  const int64_t S = std::min<int64_t>(2 * cus, kMaxFineSlots);
+  std::vector<Tile> tiles;
+  int64_t longest = 0, total = 0, longest_unit = 0, wide_cost = 0;
+  for (size_t i = 0; i < chunks.size(); ++i) {
+    const Unit& u = chunks[i];
+    const int64_t unit_steps = ceil_div(u[U_KV1], kChunkStepKeys);
+    longest_unit = std::max(longest_unit, unit_steps);
+    wide_cost += 167 * unit_steps + 870;
+    for (int64_t h = 0; h * kTileRows < (u[U_Q1] - u[U_Q0]) * int64_t(P.group); ++h) {
+      const int64_t tokens = std::min<int64_t>(
+          u[U_Q1], u[U_Q0] + (h * kTileRows + kTileRows - 1) / P.group + 1);
+      const int64_t keys = u[U_PRIOR] + tokens, steps = ceil_div(keys, kTileStepKeys);
+      tiles.push_back({int64_t(i), h, keys, steps, -1});
+      longest = std::max(longest, steps);
+      total += steps;
+    }
+  }
+  const int64_t n = int64_t(tiles.size()), units = int64_t(chunks.size());
+  if (n == 0) return;
+  const bool one_wave = n <= S;
+  int64_t piece = longest;
+  if (one_wave) {
+    auto pieces = [&](int64_t t) {
+      int64_t k = 0;
+      for (const Tile& x : tiles) k += ceil_div(x.steps, t);
+      return k;
+    };
+    int64_t t = std::min(kMinPieceSteps, longest), hi = longest;
+    while (t < hi) {
+      const int64_t mid = (t + hi) / 2;
+      if (pieces(mid) <= S) hi = mid;
+      else t = mid + 1;
+    }
+    const int64_t whole_time = longest * (n <= cus ? 65 : 93) + 700;
+    const int64_t split_time = t * (pieces(t) <= cus ? 65 : 93) + 1300;
+    if (split_time < whole_time) piece = t;
+    const int64_t wide_step = std::max<int64_t>(125, 80 + 90 * units / cus);
+    if (units <= cus && longest_unit * wide_step + 800 < std::min(whole_time, split_time)) return;
+  } else if (wide_cost <= 45 * total + 330 * n) {
+    return;
+  }
+
+  auto Q = std::make_unique<Plan>();
+  Q->mode = P.mode;
+  Q->batch = P.batch;
+  Q->num_q_heads = P.num_q_heads;
+  Q->num_kv_heads = P.num_kv_heads;
+  Q->group = P.group;
+  Q->params = P.params;
+  Q->info = P.info;
+  Q->units = P.units;
+  Q->writes = P.writes;
+  Q->merges = P.merges;
+  Q->pages_needed = P.pages_needed;
+  Q->fine_tiles = true;
+  int64_t slots = 0;
+  for (Tile& t : tiles) {
+    const int64_t k = ceil_div(t.steps, piece);
+    if (k == 1) continue;
+    const Unit& u = chunks[size_t(t.unit)];
+    t.part = slots;
+    slots += k;
+    const int32_t rec[kMergeInts] = {int32_t(u[U_G] | t.h << 16), u[U_Q0], int32_t(k),
+                                     int32_t(t.part), u[U_ROW0], u[U_Q1], 0, 0};
+    Q->chunk_merges.insert(Q->chunk_merges.end(), rec, rec + kMergeInts);
+  }
+  struct Piece { const Tile* tile; int64_t j, steps; };
+  std::vector<std::vector<Piece>> queues(kNumXcds);
+  if (!one_wave) {  // the units' queues, a unit's tiles next to each other: they read the same keys
+    for (const Tile& t : tiles) {
+      int x = 0;
+      while (t.unit >= P.xcd_map[size_t(2 * x)] + P.xcd_map[size_t(2 * x + 1)]) ++x;
+      queues[size_t(x)].push_back({&t, 0, t.steps});
+    }
+  } else {
+    // Pieces that read the same keys next to each other, the list cut into eight runs of
+    // equal cost, one per XCD, so that they share an L2; each queue its longest piece first.
+    std::vector<Piece> all;
+    for (const Tile& t : tiles) {
+      const int64_t k = ceil_div(t.steps, piece);
+      for (int64_t j = 0; j < k; ++j)
+        all.push_back({&t, j, (j + 1) * t.steps / k - j * t.steps / k});
+    }
+    std::sort(all.begin(), all.end(), [&](const Piece& x, const Piece& y) {
+      const Unit &a = chunks[size_t(x.tile->unit)], &b = chunks[size_t(y.tile->unit)];
+      if (a[U_B] != b[U_B]) return a[U_B] < b[U_B];
+      if (a[U_G] != b[U_G]) return a[U_G] < b[U_G];
+      if (x.j != y.j) return x.j < y.j;
+      if (a[U_Q0] != b[U_Q0]) return a[U_Q0] < b[U_Q0];
+      return x.tile->h < y.tile->h;
+    });
+    int64_t before = 0;
+    for (const Piece& p : all) {
+      queues[size_t((2 * before + p.steps) * kNumXcds / (2 * total))].push_back(p);
+      before += p.steps;
+    }
+    for (auto& q : queues)
+      std::stable_sort(q.begin(), q.end(),
+                       [](const Piece& a, const Piece& b) { return a.steps > b.steps; });
+  }
+  int64_t longest_queue = 0;
+  for (const auto& q : queues) {
+    Q->xcd_map.push_back(int32_t(Q->tiles.size() / kTileInts));
+    Q->xcd_map.push_back(int32_t(q.size()));
+    longest_queue = std::max(longest_queue, int64_t(q.size()));
+    for (const Piece& p : q) {
+      const Tile& t = *p.tile;
+      const Unit& u = chunks[size_t(t.unit)];
+      const int64_t k = ceil_div(t.steps, piece);
+      const int64_t kv0 = p.j * t.steps / k * kTileStepKeys;
+      const int64_t kv1 = std::min((p.j + 1) * t.steps / k * kTileStepKeys, t.keys);
+      const int32_t rec[kTileInts] = {u[U_B], int32_t(u[U_G] | t.h << 16), u[U_Q0], u[U_Q1],
+                                      u[U_ROW0], u[U_PRIOR], int32_t(kv0), int32_t(kv1),
+                                      k > 1 ? int32_t(t.part + p.j) : -1, int32_t(k)};
+      Q->tiles.insert(Q->tiles.end(), rec, rec + kTileInts);
+    }
+  }
+  Q->chunk_grid = kNumXcds * longest_queue;
+  workspace_layout(*Q, slots);
+  Q->ws_bytes = std::max(Q->ws_bytes, P.ws_bytes);
+  P.fine = std::move(Q);
+}
+
 }  // namespace
 
 libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const int32_t* q_lens,
@@ -357,21 +529,8 @@ libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const
   I.n_merge_groups = int32_t(P.merges.size() / kMergeInts);
   I.balanced = balanced ? 1 : 0;
 
-  size_t off = 0;
-  P.off_units = off;
-  off = align256(off + P.units.size() * sizeof(int32_t));
-  P.off_writes = off;
-  off = align256(off + P.writes.size() * sizeof(int32_t));
-  P.off_merges = off;
-  off = align256(off + P.merges.size() * sizeof(int32_t));
-  P.off_xcd_map = off;
-  off = align256(off + P.xcd_map.size() * sizeof(int32_t));
-  P.upload_bytes = off;
-  P.off_part_o = off;
-  off = align256(off + size_t(slots) * size_t(G) * kDim * sizeof(float));
-  P.off_part_lse = off;
-  off = align256(off + size_t(slots) * size_t(G) * sizeof(float));
-  P.ws_bytes = std::max<size_t>(off, 256);
+  workspace_layout(P, 0);
+  build_fine(chunks, P);
   return LIBRA_OK;
 }
 

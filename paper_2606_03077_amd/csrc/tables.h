@@ -21,8 +21,16 @@ enum UnitField : int {
 constexpr int kKindSingle = 0;
 constexpr int kKindChunk = 1;
 constexpr int kNumXcds = 8;  // MI355X: workgroup w is dispatched to XCD w % 8
-constexpr int kChunkStepKeys = 64;  // keys per step of the chunk kernel's key loop
-constexpr int kChunkRows = 256;  // (token, head) rows of one chunk-kernel tile
+constexpr int kChunkStepKeys = 64;  // keys per step of a query tile's cost (plan rule step 9)
+constexpr int kChunkRows = 256;  // most (token, head) rows of one query tile
+constexpr int kTileRows = 128;   // rows of a fine tile: a query tile is one or two of them
+constexpr int kTileStepKeys = 32;  // keys per step of the chunk kernel on fine tiles
+
+// Fine tiles: one record per workgroup of the chunk kernel's narrow form.  It takes rows
+// [128 h, 128 h + 128) of the query tile [q0, q1) of (sequence b, KV head g), T_GH =
+// g | h << 16, over keys [kv0, kv1): all of them, or split `part` of n.
+enum TileField : int { T_B = 0, T_GH, T_Q0, T_Q1, T_ROW0, T_PRIOR, T_KV0, T_KV1, T_PART, T_NSPLIT };
+constexpr int kTileInts = 10;
 
 // Append cache-write table: one record per (sequence, page) the new tokens touch.
 enum WriteField : int { W_B = 0, W_PAGE, W_SLOT0, W_SLOT1, W_ROW, W_PAD0, W_PAD1, W_PAD2 };
@@ -31,5 +39,8 @@ constexpr int kWriteInts = 8;
 // Split-merge table: one record per (sequence, KV head) whose KV range was split.
 enum MergeField : int { M_B = 0, M_G, M_N, M_PART, M_ROW, M_PAD0, M_PAD1, M_PAD2 };
 constexpr int kMergeInts = 8;
+
+// Merge table of split fine tiles: one record per tile of rows (T_GH as above).
+enum ChunkMergeField : int { CM_GH = 0, CM_Q0, CM_N, CM_PART, CM_ROW0, CM_Q1, CM_PAD0, CM_PAD1 };
 
 }  // namespace libra
