@@ -245,6 +245,10 @@ libra_status libra_kv_reshard_host(const void* const* src, int32_t n_src, int32_
  *    comparison, ties to the smaller c); the r-th unit a slot receives is listed at
  *    position c + r S.
  *
+ * With the default units_per_cu of 3 and no chunk rows, the decode launch may cut the rows
+ * into fewer units than the table lists (step 4 with one or two units per compute unit),
+ * where its fewer partial results are worth more than the third unit's loads in flight.
+ *
  * Unit fields (LIBRA_UNIT_INTS int32): b, g, kv_begin, kv_end, q_begin, q_end, split,
  * n_splits, part_base (-1 if unsplit), row0 (first query row of sequence b),
  * kind (0 single, 1 chunk), prior (P_b = L_b - C_b).

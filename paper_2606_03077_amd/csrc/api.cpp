@@ -296,9 +296,9 @@ libra_status upload(Plan& P, void* ws, size_t ws_bytes, hipStream_t s, bool forc
   return LIBRA_OK;
 }
 
-// The form of plan P that a workspace of ws_bytes bytes runs: with fine tiles if it is large
-// enough for them, unless it already holds the tables without (so that a call on uploaded
-// tables enqueues kernels only, whatever size it states).
+// The form of plan P that a workspace of ws_bytes bytes runs: the faster one if it is large
+// enough for it, unless it already holds the plain tables (so that a call on uploaded tables
+// enqueues kernels only, whatever size it states).
 Plan& plan_for(Plan& P, const void* ws, size_t ws_bytes) {
   if (!P.fine || ws_bytes < P.fine->ws_bytes) return P;
   return holds_tables(ws, P.id) ? P : *P.fine;
@@ -601,7 +601,7 @@ libra_status libra_splitkv_plan(const libra_plan_desc* desc, const int32_t* seq_
       delete P;
       return st;
     }
-    staging_fill(*P);
+    if (P->lens.empty()) staging_fill(*P);
     if (P->fine) staging_fill(*P->fine);
   }
   *out = P;
@@ -632,6 +632,17 @@ libra_status libra_hbm_read_rate(const void* buf, size_t bytes, int32_t reps,
 
 libra_status libra_plan_get_units(libra_plan plan, const int32_t** units_host, int32_t* n_units) {
   if (!plan || !units_host || !n_units) return set_error(LIBRA_E_INVAL, "NULL argument");
+  if (!plan->lens.empty()) {
+    std::lock_guard<std::mutex> lk(plan->upload_mu);
+    if (plan->units.empty()) {
+      try {
+        const libra_status st = build_units(*plan);
+        if (st != LIBRA_OK) return st;
+      } catch (const std::bad_alloc&) {
+        return set_error(LIBRA_E_NOMEM, "plan tables allocation failed");
+      }
+    }
+  }
   *units_host = plan->units.data();
   *n_units = plan->info.n_units;
   return LIBRA_OK;
@@ -679,9 +690,10 @@ libra_status libra_decode_attn(libra_kv_layout layout, libra_plan plan, const vo
   if (ws_bytes < plan->ws_bytes)
     return set_error(LIBRA_E_WORKSPACE, "workspace smaller than libra_plan_workspace_bytes");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  st = upload(*plan, workspace, ws_bytes, s, false);
+  Plan& P = plan_for(*plan, workspace, ws_bytes);
+  st = upload(P, workspace, ws_bytes, s, false);
   if (st != LIBRA_OK) return st;
-  return launch_attention(*layout, *plan, workspace, q, block_table, bt_stride, scale, out, lse, s);
+  return launch_attention(*layout, P, workspace, q, block_table, bt_stride, scale, out, lse, s);
 }
 
 libra_status libra_decode_attn_noalloc(libra_kv_layout layout, libra_plan plan, const void* q,
@@ -706,15 +718,17 @@ libra_status libra_decode_attn_noalloc(libra_kv_layout layout, libra_plan plan, 
   st = scratch_buffer(dev, &ws);
   if (st != LIBRA_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  // A decode plan's faster form needs no more workspace than the plan itself.
+  Plan& P = plan->fine && plan->fine->ws_bytes <= scratch_capacity() ? *plan->fine : *plan;
   {
-    std::lock_guard<std::mutex> lk(plan->upload_mu);
-    if (g_scratch_owner[dev].load() != plan->id) {
-      st = enqueue_tables(*plan, ws, s);
+    std::lock_guard<std::mutex> lk(P.upload_mu);
+    if (g_scratch_owner[dev].load() != P.id) {
+      st = enqueue_tables(P, ws, s);
       if (st != LIBRA_OK) return st;
-      g_scratch_owner[dev].store(plan->id);
+      g_scratch_owner[dev].store(P.id);
     }
   }
-  return launch_attention(*layout, *plan, ws, q, block_table, bt_stride, scale, out, lse, s,
+  return launch_attention(*layout, P, ws, q, block_table, bt_stride, scale, out, lse, s,
                           /*timed=*/false);
 }
 

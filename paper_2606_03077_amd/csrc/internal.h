@@ -50,11 +50,16 @@ struct Plan {
   // caller's stream by these events (from the pool; null otherwise).
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
 
-  // The same plan with the chunk units cut into fine tiles, where that is faster (null
-  // otherwise).  It is used when the workspace holds its tables and partial results too;
-  // this plan itself needs no more workspace than the unit, write and merge tables and the
-  // single rows' partials.  Its staging image follows this plan's, and it shares the events.
+  // The same plan in the form that is launched, where another than the unit table's is faster
+  // (null otherwise): chunk units cut into fine tiles, or rows cut into fewer single units.
+  // It is used when the workspace holds its tables and partial results too; this plan itself
+  // needs no more workspace than the unit, write and merge tables and the single rows'
+  // partials.  Its staging image follows this plan's, and it shares the events.
   std::unique_ptr<Plan> fine;
+  // Lengths of a plan whose rows are launched as fewer single units: that form needs no more
+  // workspace, so this plan's own tables are never uploaded, and its unit table is built
+  // when it is asked for (libra_plan_get_units, guarded by upload_mu).
+  std::vector<int32_t> lens;
 };
 
 struct KvLayout {
@@ -71,7 +76,9 @@ libra_status hip_error(hipError_t e, const char* what);
 
 // Plan construction (host, no HIP calls unless num_cus == 0).
 libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const int32_t* q_lens,
-                        const libra_plan_params& p, Plan* out);
+                        const libra_plan_params& p, Plan* out, bool fewer_units = true);
+// The unit table of a plan that was built without it (plan.lens).
+libra_status build_units(Plan& P);
 
 // Kernel launchers (defined next to their kernels).
 hipError_t launch_pack(const KvLayout& L, const void* k_src, const void* v_src, int64_t first,

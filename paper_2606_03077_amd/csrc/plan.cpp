@@ -18,11 +18,19 @@ using Unit = std::array<int32_t, kUnitInts>;
 // with the smallest possible largest piece.  Each extra split goes to the row with the
 // largest share pages_b / n_b (exact cross-multiplied comparison, ties to the smaller b)
 // among the rows that can still be split; a row that cannot be split now never can, as
-// only its own split count would change that.  Returns false (nsplit untouched) when the
-// rows do not fit in R or the largest piece exceeds 1.5 times the mean share.
-bool one_wave_splits(const std::vector<int64_t>& pages, const std::vector<int64_t>& single,
-                     int64_t R, const libra_plan_params& p, std::vector<int64_t>& nsplit) {
-  if (single.empty() || int64_t(single.size()) > R) return false;
+// only its own split count would change that.  Not balanced when the rows do not fit in R or
+// the largest piece exceeds 1.5 times the mean share.  For ascending budgets R: each one's
+// splits are those of the one before and some more.
+struct Apportionment {
+  int64_t R;
+  bool balanced = false;
+  std::vector<int64_t> n;  // split counts (1 for other rows), if balanced
+  int64_t largest = 0;     // pages of the largest piece
+};
+
+void one_wave_splits(const std::vector<int64_t>& pages, const std::vector<int64_t>& single,
+                     const libra_plan_params& p, std::vector<Apportionment>& budgets) {
+  if (single.empty()) return;
   std::vector<int64_t> n(pages.size(), 1);
   auto before = [&](int64_t a, int64_t b) {  // true if row a's share is served after b's
     const int64_t lhs = pages[a] * n[b], rhs = pages[b] * n[a];
@@ -31,23 +39,22 @@ bool one_wave_splits(const std::vector<int64_t>& pages, const std::vector<int64_
   };
   std::priority_queue<int64_t, std::vector<int64_t>, decltype(before)> heap(before);
   for (int64_t b : single) heap.push(b);
-  int64_t total = int64_t(single.size());
-  while (total < R && !heap.empty()) {
-    const int64_t b = heap.top();
-    heap.pop();
-    if (n[b] >= p.max_splits || pages[b] < (n[b] + 1) * int64_t(p.min_split_pages)) continue;
-    ++n[b];
-    ++total;
-    heap.push(b);
+  int64_t total = int64_t(single.size()), sum = 0;
+  for (int64_t b : single) sum += pages[b];
+  for (Apportionment& a : budgets) {
+    if (int64_t(single.size()) > a.R) continue;
+    while (total < a.R && !heap.empty()) {
+      const int64_t b = heap.top();
+      heap.pop();
+      if (n[b] >= p.max_splits || pages[b] < (n[b] + 1) * int64_t(p.min_split_pages)) continue;
+      ++n[b];
+      ++total;
+      heap.push(b);
+    }
+    for (int64_t b : single) a.largest = std::max(a.largest, ceil_div(pages[b], n[b]));
+    a.balanced = __int128(2) * a.largest * a.R <= __int128(3) * sum;
+    if (a.balanced) a.n = n;
   }
-  int64_t largest = 0, sum = 0;
-  for (int64_t b : single) {
-    largest = std::max(largest, ceil_div(pages[b], n[b]));
-    sum += pages[b];
-  }
-  if (__int128(2) * largest * R > __int128(3) * sum) return false;
-  for (int64_t b : single) nsplit[b] = n[b];
-  return true;
 }
 
 // Rule step 11: the units (in step 9's order) are dealt to S slots, each to the slot with
@@ -64,15 +71,18 @@ std::vector<Unit> place_on_slots(const std::vector<Unit>& units, const libra_pla
   };
   auto cap = [&](int64_t c) { return c < n ? (n - 1 - c) / S + 1 : int64_t(0); };
   using Entry = std::pair<int64_t, int64_t>;  // (load, slot)
+  bool equal = true;
+  for (int x = 1; x < kNumXcds; ++x) equal = equal && weight(x) == weight(0);
+  const int nheaps = equal ? 1 : kNumXcds;  // equal weights: the least (load, slot) of all
   std::array<std::priority_queue<Entry, std::vector<Entry>, std::greater<Entry>>, kNumXcds> heaps;
-  for (int64_t c = 0; c < std::min(S, n); ++c) heaps[c % kNumXcds].push({0, c});
+  for (int64_t c = 0; c < std::min(S, n); ++c) heaps[size_t(c % nheaps)].push({0, c});
   std::vector<int64_t> taken(size_t(std::min(S, n)), 0);
   std::vector<Unit> out(units.size());
   for (const Unit& u : units) {
     const int64_t cost = ceil_div(u[U_KV1], kPage) - u[U_KV0] / kPage;
     int best = -1;
     Entry be{0, 0};
-    for (int k = 0; k < kNumXcds; ++k) {
+    for (int k = 0; k < nheaps; ++k) {
       if (heaps[k].empty()) continue;
       const Entry e = heaps[k].top();
       if (best >= 0) {
@@ -100,9 +110,9 @@ void workspace_layout(Plan& P, int64_t chunk_slots) {
     off = align256(off + bytes);
     return at;
   };
-  P.off_units = place(P.units.size() * sizeof(int32_t));
+  P.off_units = place(size_t(P.info.n_units) * kUnitInts * sizeof(int32_t));
   P.off_writes = place(P.writes.size() * sizeof(int32_t));
-  P.off_merges = place(P.merges.size() * sizeof(int32_t));
+  P.off_merges = place(size_t(P.info.n_merge_groups) * kMergeInts * sizeof(int32_t));
   P.off_xcd_map = place(P.xcd_map.size() * sizeof(int32_t));
   P.off_tiles = place(P.tiles.size() * sizeof(int32_t));
   P.off_chunk_merges = place(P.chunk_merges.size() * sizeof(int32_t));
@@ -114,6 +124,23 @@ void workspace_layout(Plan& P, int64_t chunk_slots) {
   P.off_chunk_o = place(chunk_rows * kDim * sizeof(float));
   P.off_chunk_lse = place(chunk_rows * sizeof(float));
   P.ws_bytes = std::max<size_t>(off, 256);
+}
+
+// A plan of the same batch and tables, whose launch is still to be changed.
+std::unique_ptr<Plan> sibling(const Plan& P) {
+  auto Q = std::make_unique<Plan>();
+  Q->mode = P.mode;
+  Q->batch = P.batch;
+  Q->num_q_heads = P.num_q_heads;
+  Q->num_kv_heads = P.num_kv_heads;
+  Q->group = P.group;
+  Q->params = P.params;
+  Q->info = P.info;
+  Q->units = P.units;
+  Q->writes = P.writes;
+  Q->merges = P.merges;
+  Q->pages_needed = P.pages_needed;
+  return Q;
 }
 
 // Builds P.fine, the plan whose chunk launch takes fine tiles (kTileRows rows each, four
@@ -182,18 +209,7 @@ void build_fine(const std::vector<Unit>& chunks, Plan& P) {
     return;
   }
 
-  auto Q = std::make_unique<Plan>();
-  Q->mode = P.mode;
-  Q->batch = P.batch;
-  Q->num_q_heads = P.num_q_heads;
-  Q->num_kv_heads = P.num_kv_heads;
-  Q->group = P.group;
-  Q->params = P.params;
-  Q->info = P.info;
-  Q->units = P.units;
-  Q->writes = P.writes;
-  Q->merges = P.merges;
-  Q->pages_needed = P.pages_needed;
+  auto Q = sibling(P);
   Q->fine_tiles = true;
   int64_t slots = 0;
   for (Tile& t : tiles) {
@@ -266,7 +282,7 @@ void build_fine(const std::vector<Unit>& chunks, Plan& P) {
 }  // namespace
 
 libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const int32_t* q_lens,
-                        const libra_plan_params& p, Plan* out) {
+                        const libra_plan_params& p, Plan* out, bool fewer_units) {
   const int64_t B = d.batch;
   const int64_t Hkv = d.num_kv_heads;
   const int64_t G = d.num_q_heads / d.num_kv_heads;
@@ -299,54 +315,109 @@ libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const
   const int64_t chunk = W > 0 ? std::max<int64_t>(p.min_split_pages, ceil_div(W, S))
                               : int64_t(p.min_split_pages);
   std::vector<int64_t> nsplit(B, 1), slot_base(B, -1);
-  const bool balanced = one_wave_splits(pages, single, S / Hkv, p, nsplit);
-  if (!balanced)
+  // The last budget is the rule's; the others are of fewer units per CU (see the end).
+  const int64_t cus = p.num_cus;
+  std::vector<Apportionment> budgets;
+  if (fewer_units && int64_t(single.size()) == B && p.units_per_cu == 3) {
+    if (W <= 100 * cus) budgets.push_back({cus / Hkv});
+    if (W <= 400 * cus) budgets.push_back({2 * cus / Hkv});
+  }
+  budgets.push_back({S / Hkv});
+  one_wave_splits(pages, single, p, budgets);
+  const bool balanced = budgets.back().balanced;
+  if (balanced)
+    nsplit = budgets.back().n;
+  else
     for (int64_t b : single)
       nsplit[b] = std::min<int64_t>(p.max_splits, std::max<int64_t>(1, ceil_div(pages[b], chunk)));
 
   // Step 10: partial slots in ascending (b, g).
-  int64_t slots = 0;
-  for (int64_t b : single) {
-    if (nsplit[b] > 1) {
-      slot_base[b] = slots;
-      slots += nsplit[b] * Hkv;
+  auto place_slots = [&](const std::vector<int64_t>& n, std::vector<int64_t>& base) {
+    int64_t slots = 0;
+    for (int64_t b : single) {
+      base[size_t(b)] = n[size_t(b)] > 1 ? slots : -1;
+      if (n[size_t(b)] > 1) slots += n[size_t(b)] * Hkv;
     }
-  }
+    return slots;
+  };
+  const int64_t slots = place_slots(nsplit, slot_base);
   if (slots > INT32_MAX) return set_error(LIBRA_E_INVAL, "too many partial slots");
 
-  std::vector<Unit> singles, chunks;
-  for (int64_t b = 0; b < B; ++b) {
-    if (C[b] != 1) continue;
-    const int64_t n = nsplit[b];
-    for (int64_t g = 0; g < Hkv; ++g) {
-      for (int64_t j = 0; j < n; ++j) {
-        const int64_t p0 = (j * pages[b]) / n, p1 = ((j + 1) * pages[b]) / n;
-        Unit u{};
-        u[U_B] = int32_t(b);
-        u[U_G] = int32_t(g);
-        u[U_KV0] = int32_t(kPage * p0);
-        u[U_KV1] = int32_t(std::min<int64_t>(kPage * p1, L[b]));
-        u[U_Q0] = 0;
-        u[U_Q1] = 1;
-        u[U_SPLIT] = int32_t(j);
-        u[U_NSPLIT] = int32_t(n);
-        u[U_PART] = n > 1 ? int32_t(slot_base[b] + g * n) : -1;
-        u[U_ROW0] = int32_t(row0[b]);
-        u[U_KIND] = kKindSingle;
-        u[U_PRIOR] = int32_t(L[b] - 1);
-        singles.push_back(u);
+  // Steps 6, 8, 9 and 11: the single units of split counts n, on S slots.
+  auto single_units = [&](const std::vector<int64_t>& nsplit, const std::vector<int64_t>& slot_base,
+                          int64_t S) {
+    std::vector<Unit> units;
+    for (int64_t b : single) {
+      const int64_t n = nsplit[b];
+      for (int64_t g = 0; g < Hkv; ++g) {
+        for (int64_t j = 0; j < n; ++j) {
+          const int64_t p0 = (j * pages[b]) / n, p1 = ((j + 1) * pages[b]) / n;
+          Unit u{};
+          u[U_B] = int32_t(b);
+          u[U_G] = int32_t(g);
+          u[U_KV0] = int32_t(kPage * p0);
+          u[U_KV1] = int32_t(std::min<int64_t>(kPage * p1, L[b]));
+          u[U_Q0] = 0;
+          u[U_Q1] = 1;
+          u[U_SPLIT] = int32_t(j);
+          u[U_NSPLIT] = int32_t(n);
+          u[U_PART] = n > 1 ? int32_t(slot_base[b] + g * n) : -1;
+          u[U_ROW0] = int32_t(row0[b]);
+          u[U_KIND] = kKindSingle;
+          u[U_PRIOR] = int32_t(L[b] - 1);
+          units.push_back(u);
+        }
       }
     }
+    // Built in ascending (b, g, j), so equal token counts stay in that order.
+    std::vector<std::pair<int32_t, int32_t>> order(units.size());  // (-tokens, index)
+    for (size_t i = 0; i < units.size(); ++i)
+      order[i] = {units[i][U_KV0] - units[i][U_KV1], int32_t(i)};
+    std::sort(order.begin(), order.end());
+    std::vector<Unit> sorted;
+    sorted.reserve(units.size());
+    for (const auto& o : order) sorted.push_back(units[size_t(o.second)]);
+    return sorted.empty() ? sorted : place_on_slots(sorted, p, S);
+  };
+  // Fewer single units, where there are no chunk rows beside them and the default three units
+  // per CU (as many as are resident) were asked for; the public unit table stays the rule's,
+  // and the form is taken only if it needs no more workspace.  While the rows hold at most 400 pages
+  // per CU, what a unit costs besides its pages (start, wait for its slowest wave, partial
+  // result) and an uneven last few units weigh more than the third unit's loads in flight:
+  // the rows are then cut for one wave of two units per CU if step 4 can balance it, and of
+  // one if they hold at most 100 pages per CU and its largest piece is within 15% of the
+  // mean.  Measured, decode and merge, caches cold: 64 rows of ~2,048 tokens (7 heads per KV
+  // head, 217 pages per CU) 80.5 us with three units, 76.2 with two; 128 rows of 300-700
+  // tokens (64 pages) 31.2 and 26.2; 16 rows of ~2,048 (43 pages) 23.4, 22.5 and 22.2 with
+  // one; one of 40,959 (80 pages) 34.5, 34.2 and 33.5; but 32 rows (85 pages, largest piece
+  // 1.3 times the mean) 37.5, 36.5 and 38.8, and 16 of 20,000-32,000 (810 pages) 271.7,
+  // 273.8 and 296.1.
+  auto count_units = [&](const std::vector<int64_t>& n) {
+    int64_t count = 0;
+    for (int64_t b : single) count += n[size_t(b)] * Hkv;
+    return count;
+  };
+  auto count_merges = [&](const std::vector<int64_t>& n) {
+    int64_t count = 0;
+    for (int64_t b : single) count += n[size_t(b)] > 1 ? Hkv : 0;
+    return count;
+  };
+  const Apportionment* fewer = nullptr;
+  std::vector<int64_t> fewer_base(B, -1);
+  int64_t fewer_slots = 0;
+  for (size_t i = 0; i + 1 < budgets.size() && !fewer; ++i) {
+    const Apportionment& a = budgets[i];
+    if (!a.balanced || (a.R == cus / Hkv && 100 * a.largest * cus > 115 * W)) continue;
+    fewer_slots = place_slots(a.n, fewer_base);
+    if (count_units(a.n) < count_units(nsplit) && count_merges(a.n) <= count_merges(nsplit) &&
+        fewer_slots <= slots)
+      fewer = &a;
   }
-  std::sort(singles.begin(), singles.end(), [](const Unit& x, const Unit& y) {
-    const int64_t tx = x[U_KV1] - x[U_KV0], ty = y[U_KV1] - y[U_KV0];
-    if (tx != ty) return tx > ty;
-    if (x[U_B] != y[U_B]) return x[U_B] < y[U_B];
-    if (x[U_G] != y[U_G]) return x[U_G] < y[U_G];
-    return x[U_SPLIT] < y[U_SPLIT];
-  });
-  if (!singles.empty())  // step 11: CU slots for one wave, else the XCD queues
-    singles = place_on_slots(singles, p, balanced ? int64_t(p.num_cus) : int64_t(kNumXcds));
+  // Step 11: CU slots for one wave, else the XCD queues.
+  std::vector<Unit> singles;
+  if (!fewer)
+    singles = single_units(nsplit, slot_base, balanced ? int64_t(p.num_cus) : int64_t(kNumXcds));
+  std::vector<Unit> chunks;
 
   // Step 7: query tiles of chunk rows.
   const int64_t T = p.q_tile > 0 ? p.q_tile : int64_t(kChunkRows) / G;
@@ -497,27 +568,29 @@ libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const
   P.chunk_grid = int64_t(kNumXcds) * longest;
 
   // Split-merge table: every single row with n_b > 1, per KV head, ascending (b, g).
-  P.merges.clear();
-  for (int64_t b = 0; b < B; ++b) {
-    if (C[b] != 1 || nsplit[b] <= 1) continue;
-    for (int64_t g = 0; g < Hkv; ++g) {
-      const int32_t rec[kMergeInts] = {int32_t(b), int32_t(g), int32_t(nsplit[b]),
-                                       int32_t(slot_base[b] + g * nsplit[b]), int32_t(row0[b]),
-                                       0, 0, 0};
-      P.merges.insert(P.merges.end(), rec, rec + kMergeInts);
+  auto merge_table = [&](const std::vector<int64_t>& n, const std::vector<int64_t>& base) {
+    std::vector<int32_t> merges;
+    for (int64_t b : single) {
+      if (n[b] <= 1) continue;
+      for (int64_t g = 0; g < Hkv; ++g) {
+        const int32_t rec[kMergeInts] = {int32_t(b), int32_t(g), int32_t(n[b]),
+                                         int32_t(base[b] + g * n[b]), int32_t(row0[b]), 0, 0, 0};
+        merges.insert(merges.end(), rec, rec + kMergeInts);
+      }
     }
-  }
+    return merges;
+  };
+  if (!fewer) P.merges = merge_table(nsplit, slot_base);
 
   // Block-table columns the kernels read: every unit's pages and every written page.
   P.pages_needed = 0;
-  for (size_t i = 0; i < P.units.size(); i += kUnitInts)
-    P.pages_needed = std::max<int64_t>(P.pages_needed, ceil_div(P.units[i + U_KV1], kPage));
+  for (int64_t b = 0; b < B; ++b) P.pages_needed = std::max(P.pages_needed, pages[b]);
   for (size_t i = 0; i < P.writes.size(); i += kWriteInts)
     P.pages_needed = std::max<int64_t>(P.pages_needed, int64_t(P.writes[i + W_PAGE]) + 1);
 
   libra_plan_info& I = P.info;
   std::memset(&I, 0, sizeof(I));
-  I.n_single = int32_t(singles.size());
+  I.n_single = int32_t(count_units(nsplit));
   I.n_chunk = int32_t(chunks.size());
   I.n_units = I.n_single + I.n_chunk;
   I.n_partial_slots = int32_t(slots);
@@ -526,12 +599,41 @@ libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const
   I.n_rows = int32_t(rows);
   I.n_write_tiles = int32_t(P.writes.size() / kWriteInts);
   I.num_cus = p.num_cus;
-  I.n_merge_groups = int32_t(P.merges.size() / kMergeInts);
+  I.n_merge_groups = int32_t(count_merges(nsplit));
   I.balanced = balanced ? 1 : 0;
 
   workspace_layout(P, 0);
   build_fine(chunks, P);
+  if (fewer) {
+    auto Q = sibling(P);
+    for (const Unit& u : single_units(fewer->n, fewer_base, cus))
+      Q->units.insert(Q->units.end(), u.begin(), u.end());
+    Q->merges = merge_table(fewer->n, fewer_base);
+    Q->info.n_units = Q->info.n_single = int32_t(Q->units.size() / kUnitInts);
+    Q->info.n_partial_slots = int32_t(fewer_slots);
+    Q->info.n_merge_groups = int32_t(Q->merges.size() / kMergeInts);
+    Q->xcd_map = P.xcd_map;
+    workspace_layout(*Q, 0);  // every part is at most as large as P's
+    Q->ws_bytes = P.ws_bytes;
+    P.lens.assign(seq_lens, seq_lens + B);
+    P.upload_bytes = 0;
+    P.fine = std::move(Q);
+  }
   return LIBRA_OK;
+}
+
+libra_status build_units(Plan& P) {
+  libra_plan_desc d{};
+  d.mode = P.mode;
+  d.batch = P.batch;
+  d.num_q_heads = P.num_q_heads;
+  d.num_kv_heads = P.num_kv_heads;
+  const std::vector<int32_t> ones(P.lens.size(), 1);
+  Plan whole;
+  const libra_status st = build_plan(d, P.lens.data(), d.mode == LIBRA_MODE_APPEND ? ones.data() : nullptr,
+                                     P.params, &whole, false);
+  if (st == LIBRA_OK) P.units = std::move(whole.units);
+  return st;
 }
 
 }  // namespace libra
