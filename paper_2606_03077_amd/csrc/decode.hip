@@ -234,12 +234,33 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(LIBRA_
     };
 
     // Ring of kDepth pages: page k + kDepth is issued into the registers page k has
-    // just been consumed from, so kDepth - 1 pages stay in flight during the math.
+    // just been consumed from, so kDepth - 1 pages stay in flight during the math.  Its
+    // steady state has no branch between a page's use and the next issue, and is entered
+    // only with the ring filled: with conditional issues the compiler waits for every load
+    // outstanding before it uses the oldest.  Its pages are whole, as a sequence's last page
+    // is never among them.  Against one conditional loop, decode and merge with cold caches:
+    // 96 rows of ~4,096 tokens (542 pages per CU) 193 us, now 187 us, 16 rows of ~2,048
+    // (43 pages) 22.9 and 22.5 us; 28-layer step of 16 requests 713 and 697 us; the
+    // long-tailed batch is at the device's read rate either way (832-851 us).  Rings of
+    // three or four pages (184 and 221 registers) are no faster.
     PageRegs ring[kDepth];
+    int k0 = 0;
+    if (nw >= 2 * kDepth) {
 #pragma unroll
-    for (int j = 0; j < kDepth; ++j)
-      if (j < nw) issue(j, ring[j]);
-    for (int k = 0; k < nw; k += kDepth) {
+      for (int j = 0; j < kDepth; ++j) issue(j, ring[j]);
+      for (; k0 + 2 * kDepth <= nw; k0 += kDepth) {
+#pragma unroll
+        for (int j = 0; j < kDepth; ++j) {
+          process_page(ring[j], kPage, quad, qop, A.sl2, sm, acc);
+          issue(k0 + j + kDepth, ring[j]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < kDepth; ++j)
+        if (j < nw) issue(j, ring[j]);
+    }
+    for (int k = k0; k < nw; k += kDepth) {
 #pragma unroll
       for (int j = 0; j < kDepth; ++j) {
         if (k + j < nw) {
