@@ -155,12 +155,14 @@ std::unique_ptr<Plan> sibling(const Plan& P) {
 // * a 64-key step of a wide workgroup takes 1.25 us while half of the CUs are idle, 1.67 us
 //   when all are busy, and a workgroup 8-9 us besides (dispatch, first loads, stores);
 // * a 32-key step of a fine tile takes 0.65 us alone on a CU and 0.91-0.93 us beside
-//   another, a tile 3.3 us of its CU besides (7 us by itself), a merge 6 us.
-// So full tiles in many waves stay wide (40,960-token prefill: 13.8 ms against 15.0 ms), and
-// fine tiles take launches that leave CUs idle (333 tokens on 16,001: 129 us against 326 us;
-// 800 tokens on 16,000: 267 against 340 us; 4 x 8 tokens on 30,000: 54 against 583 us),
-// query tiles of at most 128 rows (128 x 20 tokens on 2,000, 4 heads per KV head: 218
-// against 267 us) and short ones (64 x 100 tokens on 500: 77 against 80 us).
+//   another, a tile 3.3 us of its CU besides (7 us by itself), a split launch and its merge
+//   13 us more (496 tokens on 431, at most 29 steps: 25 us whole, 35 us split in four).
+// So full tiles in many waves stay wide from about 15 steps on (20 prompts of 2,040 tokens
+// 974 us against 984 us, 10 of 4,080 1,642 and 1,716 us, 40,960-token prefill 13.8 and
+// 15.0 ms), and fine tiles take shorter ones (80 prompts of 510 tokens 470 us against 515 us,
+// 64 x 100 tokens on 500 78 and 81 us), query tiles of at most 128 rows (128 x 20 tokens on
+// 2,000, 4 heads per KV head: 218 and 266 us) and launches that leave CUs idle (333 tokens on
+// 16,001: 129 and 326 us; 800 on 16,000: 267 and 340 us; 4 x 8 on 30,000: 54 and 583 us).
 constexpr int64_t kMinPieceSteps = 8;
 constexpr int64_t kMaxFineSlots = 2048;  // bounds the partial results (64.5 KiB each)
 
@@ -174,7 +176,7 @@ void build_fine(const std::vector<Unit>& chunks, Plan& P) {
     const Unit& u = chunks[i];
     const int64_t unit_steps = ceil_div(u[U_KV1], kChunkStepKeys);
     longest_unit = std::max(longest_unit, unit_steps);
-    wide_cost += 167 * unit_steps + 870;
+    wide_cost += 167 * unit_steps + 840;
     for (int64_t h = 0; h * kTileRows < (u[U_Q1] - u[U_Q0]) * int64_t(P.group); ++h) {
       const int64_t tokens = std::min<int64_t>(
           u[U_Q1], u[U_Q0] + (h * kTileRows + kTileRows - 1) / P.group + 1);
@@ -201,11 +203,11 @@ void build_fine(const std::vector<Unit>& chunks, Plan& P) {
       else t = mid + 1;
     }
     const int64_t whole_time = longest * (n <= cus ? 65 : 93) + 700;
-    const int64_t split_time = t * (pieces(t) <= cus ? 65 : 93) + 1300;
+    const int64_t split_time = t * (pieces(t) <= cus ? 65 : 93) + 2000;
     if (split_time < whole_time) piece = t;
     const int64_t wide_step = std::max<int64_t>(125, 80 + 90 * units / cus);
     if (units <= cus && longest_unit * wide_step + 800 < std::min(whole_time, split_time)) return;
-  } else if (wide_cost <= 45 * total + 330 * n) {
+  } else if (wide_cost <= 46 * total + 330 * n) {
     return;
   }
 
