@@ -505,7 +505,8 @@ void chunk_kernel(ChunkArgs A) {
             buf[r * 16 + (c ^ (r & 15))];
       }
     }
-    if (hh == 0) A.part_lse[prow + col] = ls > 0.f ? m + log2f(ls) : -INFINITY;
+    // -inf only where the row saw no key: a NaN sum gives a NaN, which the merge keeps.
+    if (hh == 0) A.part_lse[prow + col] = ls == 0.f ? -INFINITY : m + log2f(ls);
     return;
   }
 #pragma unroll

@@ -142,7 +142,10 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(MergeArgs A) {
 // four to a row, thread t of a group channels 4 t .. + 3.  Group k of a row folds splits k,
 // k + 4, ... eight at a time (all loads of a batch in flight), and the groups combine
 // through LDS.  Latency-bound: many small blocks and at most ceil(n / 32) dependent rounds
-// of loads.
+// of loads.  A split without a key of the row (lse_j = -inf) is left out by its weight and
+// its partial (which may hold another row's NaN); a NaN lse_j or partial of a split that
+// the row sees makes the row NaN, as it does where keys are not split: maxima ignore NaN, so
+// no batch or group is skipped by its maximum.
 constexpr int kRowGroups = 4;
 constexpr int kMergeRows = kThreads / (32 * kRowGroups);
 
@@ -181,13 +184,13 @@ __global__ __launch_bounds__(kThreads) void chunk_merge_kernel(MergeArgs A) {
       float Mc = M;
 #pragma unroll
       for (int jj = 0; jj < kBatch; ++jj) Mc = fmaxf(Mc, lj[jj]);
-      if (Mc == -INFINITY) continue;
-      const float s = __builtin_amdgcn_exp2f(M - Mc);  // 0 while M = -inf
+      const float s = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mc);
       wsum *= s;
       acc *= s;
 #pragma unroll
       for (int jj = 0; jj < kBatch; ++jj) {
-        const float w = __builtin_amdgcn_exp2f(lj[jj] - Mc);  // 0 for empty or absent splits
+        if (lj[jj] == -INFINITY) continue;  // empty or absent split
+        const float w = __builtin_amdgcn_exp2f(lj[jj] - Mc);
         wsum += w;
         acc += w * x[jj];
       }
@@ -205,8 +208,8 @@ __global__ __launch_bounds__(kThreads) void chunk_merge_kernel(MergeArgs A) {
   for (int k = 1; k < kRowGroups; ++k) {
     const float Mk = red_m[lr][k];
     const float Mn = fmaxf(M, Mk);
-    if (Mn == -INFINITY) continue;
-    const float a = __builtin_amdgcn_exp2f(M - Mn), b = __builtin_amdgcn_exp2f(Mk - Mn);
+    const float a = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
+    const float b = Mk == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(Mk - Mn);
     wsum = wsum * a + red_w[lr][k] * b;
     acc = acc * a + red_acc[lr][k][t] * b;
     M = Mn;

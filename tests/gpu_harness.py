@@ -69,6 +69,23 @@ def plan_for(batch: wl.Batch, **params):
                                     batch.seq_lens.tolist(), q_lens, **params)
 
 
+def plain_workspace(plan, group: int = 4) -> int:
+    """Bytes of workspace that hold an append plan's unit, write and merge tables and the
+    partial results of its split decode rows, and nothing for cut chunk tiles."""
+    info = libra.libra_plan_get_info(plan)
+    up = lambda n: -(-n // 256) * 256
+    units = libra.libra_plan_get_units(plan)
+    slots = info["n_partial_slots"] * group
+    return (up(4 * units.size) + up(32 * info["n_write_tiles"]) + up(32 * info["n_merge_groups"])
+            + 256 + up(512 * slots) + up(4 * slots))
+
+
+def chunk_partials(plan, group: int = 4) -> int:
+    """Partial results (of 128 rows each) that a full workspace holds for cut chunk tiles.
+    For plans whose tables take less than one partial result (64.5 KiB)."""
+    return (libra.libra_plan_workspace_bytes(plan) - plain_workspace(plan, group)) // (128 * 129 * 4)
+
+
 def run(batch: wl.Batch, cache: DeviceCache = None, plan_params=None, repeat: int = 1):
     """Runs decode or append; returns (out f64 [rows,Hq,128], lse f64 [rows,Hq], cache, raw)."""
     cache = cache or DeviceCache(batch)
