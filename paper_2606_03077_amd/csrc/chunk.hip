@@ -45,6 +45,7 @@
 // Skipping the ring's copies past the last key, starting the first copies from scalar page
 // ids and storing whole rows through LDS took 32 prompts of 64-2,048 tokens (40/8 heads)
 // from 860 us to 820 us.
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 
@@ -278,8 +279,10 @@ void chunk_kernel(ChunkArgs A) {
   };
 
   // Causal / length mask of step n; on the first step (exact) also the running maximum
-  // (later steps check their probabilities instead, in pair()).  A row that sees any key
-  // of [kv0, kv1) sees kv0, so a maximum still -inf after the first step stays so.
+  // (later steps check their probabilities instead, in pair()).  While no finite score has
+  // come (a row without keys here, or whose first keys score -inf), the offset is the
+  // largest float: scores of -inf still give 0, and the first finite one gives infinity,
+  // which makes pair() set the maximum.
   auto prepare = [&](int key0, f32x16 (&s)[kPairs], float& neg_m, bool exact) {
     if (key0 > mask_key0) {
 #pragma unroll
@@ -297,7 +300,7 @@ void chunk_kernel(ChunkArgs A) {
       float mc = fmaxf(mloc * A.sl2, m);
       m = fmaxf(mc, __shfl_xor(mc, 32));
     }
-    neg_m = m == -INFINITY ? 0.f : -m;
+    neg_m = m == -INFINITY ? FLT_MAX : -m;
   };
   // Moves the running maximum to cover page pair P's scores (rare): rescales l and the
   // accumulators by 2^(m_old - m_new).
@@ -312,7 +315,7 @@ void chunk_kernel(ChunkArgs A) {
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) acc[cb] *= alpha;
     m = mc;
-    neg_m = m == -INFINITY ? 0.f : -m;
+    neg_m = m == -INFINITY ? FLT_MAX : -m;
   };
 
   // Page pair P of step n: probabilities (consuming s[P]), step n + 1's scores of the

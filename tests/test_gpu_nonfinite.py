@@ -1,4 +1,4 @@
-"""NaN in the inputs of an append whose chunk tiles are cut into key ranges.
+"""NaN and infinity in the inputs of an append whose chunk tiles are cut into key ranges.
 
 A row that sees a NaN score or value has no finite result, whatever its keys were cut into:
 its output is NaN and its LSE -inf, with the partials merged (full workspace) and unsplit (a
@@ -65,3 +65,30 @@ def test_nan_reaches_the_rows_that_see_it(length, cus, splits, where, small_ws):
         assert np.isneginf(lse[bad]).all()
     H.assert_parity(o[~bad][:, None], lse[~bad][:, None], ro[~bad][:, None], rl[~bad][:, None],
                     label=f"rows beside a NaN {where}, {splits} splits")
+
+
+@pytest.mark.parametrize("cus,splits", [(2, 2), (4, 4)])
+@pytest.mark.parametrize("at", ["start", "piece", "both"])
+@pytest.mark.parametrize("small_ws", [False, True])
+def test_keys_masked_by_infinity(cus, splits, at, small_ws):
+    """Keys that a program masks with an infinite channel score -inf: whole first steps of a
+    tile or of one of its key ranges give no maximum, which the steps after it then set."""
+    length = 3072
+    H.say(f"[case] -inf keys at {at} cus={cus} splits={splits} small={small_ws}")
+    b = wl.custom_batch([length], q_lens=[NEW], num_q_heads=HQ, num_kv_heads=HKV, seed=6)
+    b.q[:, :, 0] = wl.f32_to_bf16_bits(np.float32(1.0))
+    starts = {"start": [0], "piece": [length // 2], "both": [0, length // 2]}[at]
+    for s in starts:
+        for p in range(s // 16, s // 16 + 4):               # a step of 64 keys
+            b.k_pages[b.block_table[0, p], :, :, 0] = wl.f32_to_bf16_bits(np.float32(-np.inf))
+    ro, rl, _, _ = oracle.append_ref(b.q, b.k_new, b.v_new, b.k_pages, b.v_pages, b.block_table,
+                                     b.seq_lens, b.q_lens, b.scale)
+    assert np.isfinite(ro).all() and np.isfinite(rl).all()
+    plan = H.plan_for(b, num_cus=cus)
+    assert H.chunk_partials(plan) == HKV * splits
+    ws = libra.alloc_workspace(plan)
+    if small_ws:
+        ws = ws[:H.plain_workspace(plan)]
+    o, lse = append(b, plan, ws)
+    libra.libra_plan_destroy(plan)
+    H.assert_parity(o, lse, ro, rl, label=f"-inf keys at {at}, {splits} splits")
