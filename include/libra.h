@@ -327,11 +327,11 @@ libra_status libra_hbm_read_rate(const void* buf, size_t bytes, int32_t reps,
 /* Host view of the unit table (valid until libra_plan_destroy). */
 libra_status libra_plan_get_units(libra_plan plan, const int32_t** units_host, int32_t* n_units);
 libra_status libra_plan_get_info(libra_plan plan, libra_plan_info* info);
-/* Bytes of device workspace the plan's calls need (unit, write, merge and XCD-queue tables
- * and the float32 partial results of split rows).  An append plan whose chunk tiles are cut
- * further (step 7) counts the finer tables and partial results too, at most about 33 MB
- * per 256 compute units (64.5 KiB for each of up to 2 num_cus partials, at most 2048); it
- * also runs, unsplit, in a workspace too small for those but large enough for the rest. */
+/* Bytes of device workspace the plan's calls need (unit, write and merge tables and the
+ * float32 partial results of split rows).  An append plan whose chunk tiles are cut further
+ * (step 7) counts the finer tables and partial results too, at most about 33 MB per 256
+ * compute units (64.5 KiB for each of up to 2 num_cus partials, at most 2048); it also runs,
+ * unsplit, in a workspace too small for those but large enough for the rest. */
 size_t libra_plan_workspace_bytes(libra_plan plan);
 /* Copies the plan's tables into `workspace` (device) on `stream`.  Decode / append calls
  * do this themselves unless this plan was the last one to upload to that address;

@@ -255,7 +255,6 @@ void staging_fill(Plan& P) {
   put(P.off_tiles, P.tiles);
   put(P.off_writes, P.writes);
   put(P.off_merges, P.merges);
-  put(P.off_xcd_map, P.xcd_map);
   put(P.off_chunk_merges, P.chunk_merges);
 }
 
@@ -654,7 +653,7 @@ libra_status libra_plan_get_info(libra_plan plan, libra_plan_info* info) {
   return LIBRA_OK;
 }
 
-size_t libra_plan_workspace_bytes(libra_plan plan) { 
+size_t libra_plan_workspace_bytes(libra_plan plan) {
   if (!plan) return 0;
   return plan->fine ? plan->fine->ws_bytes : plan->ws_bytes;
 }

@@ -28,11 +28,10 @@ struct Plan {
   std::vector<int32_t> tiles;   // fine tiles, kTileInts each
   std::vector<int32_t> chunk_merges;  // kMergeInts per fine tile whose keys are split
 
-  // Workspace image: [units | writes | merges | xcd map | fine tiles | chunk merges | partial
-  // o | partial lse | chunk partial o | chunk partial lse], 256-B aligned.
-  size_t off_units = 0, off_tiles = 0, off_writes = 0, off_merges = 0, off_xcd_map = 0,
-         off_chunk_merges = 0, off_part_o = 0, off_part_lse = 0, off_chunk_o = 0,
-         off_chunk_lse = 0;
+  // Workspace image: [units | writes | merges | fine tiles | chunk merges | partial o |
+  // partial lse | chunk partial o | chunk partial lse], 256-B aligned.
+  size_t off_units = 0, off_tiles = 0, off_writes = 0, off_merges = 0, off_chunk_merges = 0,
+         off_part_o = 0, off_part_lse = 0, off_chunk_o = 0, off_chunk_lse = 0;
   size_t ws_bytes = 0;
   size_t upload_bytes = 0;  // bytes of the image that come from the host (up to partial o)
   int64_t pages_needed = 0; // block-table columns the units and writes read (per row, max)
@@ -42,7 +41,7 @@ struct Plan {
   // The pinned image and the event come from the library's pool at plan creation and go
   // back to it when the plan is destroyed; both stay null without a visible device.
   std::mutex upload_mu;
-  void* pinned = nullptr;         // host staging copy of [units | writes | merges | xcd map]
+  void* pinned = nullptr;         // host staging copy of the tables
   size_t pinned_capacity = 0;
   hipEvent_t upload_done = nullptr;
   // Plans with both decode rows and chunk tiles run the two launches concurrently: the

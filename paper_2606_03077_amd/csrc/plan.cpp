@@ -113,7 +113,6 @@ void workspace_layout(Plan& P, int64_t chunk_slots) {
   P.off_units = place(size_t(P.info.n_units) * kUnitInts * sizeof(int32_t));
   P.off_writes = place(P.writes.size() * sizeof(int32_t));
   P.off_merges = place(size_t(P.info.n_merge_groups) * kMergeInts * sizeof(int32_t));
-  P.off_xcd_map = place(P.xcd_map.size() * sizeof(int32_t));
   P.off_tiles = place(P.tiles.size() * sizeof(int32_t));
   P.off_chunk_merges = place(P.chunk_merges.size() * sizeof(int32_t));
   P.upload_bytes = off;
