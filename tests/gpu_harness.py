@@ -77,7 +77,7 @@ def plain_workspace(plan, group: int = 4) -> int:
     units = libra.libra_plan_get_units(plan)
     slots = info["n_partial_slots"] * group
     return (up(4 * units.size) + up(32 * info["n_write_tiles"]) + up(32 * info["n_merge_groups"])
-            + 256 + up(512 * slots) + up(4 * slots))
+            + up(512 * slots) + up(4 * slots))
 
 
 def chunk_partials(plan, group: int = 4) -> int:

@@ -42,11 +42,7 @@ def test_fine_tiles(lens, new, hq, hkv, cus, small_ws):
     plan = H.plan_for(b, num_cus=cus)
     ws = libra.alloc_workspace(plan)
     if small_ws:                                  # what a plan of whole tiles needs
-        info = libra.libra_plan_get_info(plan)
-        up = lambda n: -(-n // 256) * 256
-        slots = info["n_partial_slots"] * (hq // hkv)
-        need = (up(48 * info["n_units"]) + up(32 * info["n_write_tiles"])
-                + up(32 * info["n_merge_groups"]) + 256 + up(512 * slots) + up(4 * slots))
+        need = H.plain_workspace(plan, hq // hkv)
         assert need <= ws.numel()
         ws = ws[:need]
     rows = b.q.shape[0]
