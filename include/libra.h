@@ -337,7 +337,9 @@ size_t libra_plan_workspace_bytes(libra_plan plan);
  * do this themselves unless this plan was the last one to upload to that address;
  * calling it explicitly once per batch step lets every layer's call skip it.  The
  * workspace then belongs to this plan until another plan uploads to it (plans may take
- * turns on one workspace; each call of another plan re-uploads).  Calls that share a
+ * turns on one workspace; each call of another plan re-uploads).  Calls may state any
+ * ws_bytes that the plan accepts (libra_plan_workspace_bytes); none of this plan's calls or
+ * uploads overwrites tables that another of its calls reads.  Calls that share a
  * workspace must be ordered on one stream.  Memory that is freed and allocated again at
  * the same address, or written by anything but this library, no longer holds the tables:
  * call libra_plan_upload on it before the next decode / append call. */

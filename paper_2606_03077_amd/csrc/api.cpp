@@ -127,10 +127,11 @@ std::atomic<uint64_t> g_next_plan_id{1};
 constexpr int kMaxScratchOwners = 64;
 std::atomic<uint64_t> g_scratch_owner[kMaxScratchOwners] = {};
 
-bool holds_tables(const void* ws, uint64_t id) {
+// The id of the plan (or form of a plan) that last uploaded to ws, 0 if none.
+uint64_t tables_of(const void* ws) {
   std::lock_guard<std::mutex> lk(g_ws.mu);
   auto it = g_ws.owner.find(reinterpret_cast<uintptr_t>(ws));
-  return it != g_ws.owner.end() && it->second == id;
+  return it != g_ws.owner.end() ? it->second : 0;
 }
 
 // Pinned staging images and upload events, owned by the library and reused by plans.
@@ -248,8 +249,8 @@ void staging_fill(Plan& P) {
   if (!P.pinned) return;
   char* h = static_cast<char*>(P.pinned);
   std::memset(h, 0, P.upload_bytes);
-  auto put = [h](size_t off, const std::vector<int32_t>& v) {
-    if (!v.empty()) std::memcpy(h + off, v.data(), v.size() * sizeof(int32_t));
+  auto put = [&](size_t off, const std::vector<int32_t>& v) {
+    if (!v.empty()) std::memcpy(h + (off - P.upload_off), v.data(), v.size() * sizeof(int32_t));
   };
   put(P.off_units, P.units);
   put(P.off_tiles, P.tiles);
@@ -258,49 +259,61 @@ void staging_fill(Plan& P) {
   put(P.off_chunk_merges, P.chunk_merges);
 }
 
-// Enqueues the copy of the plan's pinned table image to ws and records its event.
-// Allocates nothing.  Caller holds P.upload_mu.
-libra_status enqueue_tables(Plan& P, void* ws, hipStream_t s) {
+// Enqueues the copy of the plan's pinned table image to ws (after the image of the plan that
+// it is a form of, if its launch reads that too) and records its event.  Allocates nothing.
+// Caller holds the plan's upload_mu.
+libra_status enqueue_tables(const Plan& P, void* ws, hipStream_t s) {
   if (!P.upload_done)
     return set_error(LIBRA_E_INVAL,
                      "plan was built without a visible HIP device; it cannot run on one");
-  hipError_t e;
+  auto copy = [&](const Plan& from, size_t bytes) {
+    if (bytes == 0) return hipSuccess;
+    return hipMemcpyAsync(static_cast<char*>(ws) + from.upload_off, from.pinned, bytes,
+                          hipMemcpyHostToDevice, s);
+  };
+  hipError_t e = hipSuccess;
   {
     ProfScope ps(LIBRA_KERNEL_UPLOAD, s, true);
-    if (P.upload_bytes > 0) {
-      e = hipMemcpyAsync(ws, P.pinned, P.upload_bytes, hipMemcpyHostToDevice, s);
-      if (e != hipSuccess) return hip_error(e, "hipMemcpyAsync(plan tables)");
+    if (!P.base) {
+      e = copy(P, P.upload_bytes);
+    } else if (P.base->upload_bytes == P.upload_off) {  // neighbours, as their images are
+      e = copy(*P.base, P.base->upload_bytes + P.upload_bytes);
+    } else {
+      e = copy(*P.base, P.base->upload_bytes);
+      if (e == hipSuccess) e = copy(P, P.upload_bytes);
     }
   }
+  if (e != hipSuccess) return hip_error(e, "hipMemcpyAsync(plan tables)");
   e = hipEventRecord(P.upload_done, s);
   if (e != hipSuccess) return hip_error(e, "hipEventRecord");
   return LIBRA_OK;
 }
 
-// Copies the plan's tables into ws unless ws already holds them (or always, if forced).
-libra_status upload(Plan& P, void* ws, size_t ws_bytes, hipStream_t s, bool force = true) {
+// Picks the form of plan P that runs in a workspace of ws_bytes bytes and copies its tables
+// there unless they are there already (or always, if forced).  The faster form is taken if
+// the workspace is large enough for it; a call whose workspace holds the plain tables runs
+// the plain form, so that a call on uploaded tables enqueues kernels only, whatever size
+// it states: the plain tables are there with the fine tiles' as well.
+libra_status upload(Plan& P, void* ws, size_t ws_bytes, hipStream_t s, bool force,
+                    const Plan** form) {
   std::lock_guard<std::mutex> lk(P.upload_mu);
-  if (!force && holds_tables(ws, P.id)) return LIBRA_OK;
   if (!ws) return set_error(LIBRA_E_INVAL, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(ws) % kWorkspaceAlign)
     return set_error(LIBRA_E_INVAL, "workspace must be 256-byte aligned");
   if (ws_bytes < P.ws_bytes)
     return set_error(LIBRA_E_WORKSPACE, "workspace smaller than libra_plan_workspace_bytes");
-  libra_status st = enqueue_tables(P, ws, s);
+  const uint64_t held = force ? 0 : tables_of(ws);
+  const bool fits = P.fine && ws_bytes >= P.fine->ws_bytes;
+  const Plan& Q = fits && held != P.id ? *P.fine : P;
+  *form = &Q;
+  if (held == Q.id || (P.fine && P.fine->base && held == P.fine->id)) return LIBRA_OK;
+  libra_status st = enqueue_tables(Q, ws, s);
   if (st != LIBRA_OK) return st;
   {
     std::lock_guard<std::mutex> lk2(g_ws.mu);
-    g_ws.owner[reinterpret_cast<uintptr_t>(ws)] = P.id;
+    g_ws.owner[reinterpret_cast<uintptr_t>(ws)] = Q.id;
   }
   return LIBRA_OK;
-}
-
-// The form of plan P that a workspace of ws_bytes bytes runs: the faster one if it is large
-// enough for it, unless it already holds the plain tables (so that a call on uploaded tables
-// enqueues kernels only, whatever size it states).
-Plan& plan_for(Plan& P, const void* ws, size_t ws_bytes) {
-  if (!P.fine || ws_bytes < P.fine->ws_bytes) return P;
-  return holds_tables(ws, P.id) ? P : *P.fine;
 }
 
 libra_status check_call(const KvLayout* L, const Plan* P, int mode, const void* q,
@@ -660,8 +673,8 @@ size_t libra_plan_workspace_bytes(libra_plan plan) {
 
 libra_status libra_plan_upload(libra_plan plan, void* workspace, size_t ws_bytes, void* stream) {
   if (!plan) return set_error(LIBRA_E_INVAL, "plan is NULL");
-  Plan& P = plan->fine && ws_bytes >= plan->fine->ws_bytes ? *plan->fine : *plan;
-  return upload(P, workspace, ws_bytes, static_cast<hipStream_t>(stream));
+  const Plan* form = nullptr;
+  return upload(*plan, workspace, ws_bytes, static_cast<hipStream_t>(stream), true, &form);
 }
 
 void libra_plan_destroy(libra_plan plan) {
@@ -689,9 +702,10 @@ libra_status libra_decode_attn(libra_kv_layout layout, libra_plan plan, const vo
   if (ws_bytes < plan->ws_bytes)
     return set_error(LIBRA_E_WORKSPACE, "workspace smaller than libra_plan_workspace_bytes");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Plan& P = plan_for(*plan, workspace, ws_bytes);
-  st = upload(P, workspace, ws_bytes, s, false);
+  const Plan* form = nullptr;
+  st = upload(*plan, workspace, ws_bytes, s, false, &form);
   if (st != LIBRA_OK) return st;
+  const Plan& P = *form;
   return launch_attention(*layout, P, workspace, q, block_table, bt_stride, scale, out, lse, s);
 }
 
@@ -718,9 +732,9 @@ libra_status libra_decode_attn_noalloc(libra_kv_layout layout, libra_plan plan, 
   if (st != LIBRA_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   // A decode plan's faster form needs no more workspace than the plan itself.
-  Plan& P = plan->fine && plan->fine->ws_bytes <= scratch_capacity() ? *plan->fine : *plan;
+  const Plan& P = plan->fine ? *plan->fine : *plan;
   {
-    std::lock_guard<std::mutex> lk(P.upload_mu);
+    std::lock_guard<std::mutex> lk(plan->upload_mu);
     if (g_scratch_owner[dev].load() != P.id) {
       st = enqueue_tables(P, ws, s);
       if (st != LIBRA_OK) return st;
@@ -747,9 +761,10 @@ libra_status libra_append_attn(libra_kv_layout layout, libra_plan plan, const vo
   if (ws_bytes < plan->ws_bytes)
     return set_error(LIBRA_E_WORKSPACE, "workspace smaller than libra_plan_workspace_bytes");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Plan& P = plan_for(*plan, workspace, ws_bytes);
-  st = upload(P, workspace, ws_bytes, s, false);
+  const Plan* form = nullptr;
+  st = upload(*plan, workspace, ws_bytes, s, false, &form);
   if (st != LIBRA_OK) return st;
+  const Plan& P = *form;
   hipError_t e;
   {
     ProfScope ps(LIBRA_KERNEL_CACHE_WRITE, s, P.info.n_write_tiles > 0);

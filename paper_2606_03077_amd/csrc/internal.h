@@ -28,12 +28,15 @@ struct Plan {
   std::vector<int32_t> tiles;   // fine tiles, kTileInts each
   std::vector<int32_t> chunk_merges;  // kMergeInts per fine tile whose keys are split
 
-  // Workspace image: [units | writes | merges | fine tiles | chunk merges | partial o |
-  // partial lse | chunk partial o | chunk partial lse], 256-B aligned.
+  // Workspace: [units | writes | merges | partial o | partial lse], and behind it, where
+  // chunk units are launched as fine tiles, [fine tiles | chunk merges | chunk partial o |
+  // chunk partial lse]; all 256-B aligned.
   size_t off_units = 0, off_tiles = 0, off_writes = 0, off_merges = 0, off_chunk_merges = 0,
          off_part_o = 0, off_part_lse = 0, off_chunk_o = 0, off_chunk_lse = 0;
   size_t ws_bytes = 0;
-  size_t upload_bytes = 0;  // bytes of the image that come from the host (up to partial o)
+  // The tables come from the host: upload_bytes bytes of staging image to upload_off of the
+  // workspace.
+  size_t upload_off = 0, upload_bytes = 0;
   int64_t pages_needed = 0; // block-table columns the units and writes read (per row, max)
   uint64_t id = 0;          // process-unique, set at creation: which plan a workspace holds
 
@@ -51,10 +54,12 @@ struct Plan {
 
   // The same plan in the form that is launched, where another than the unit table's is faster
   // (null otherwise): chunk units cut into fine tiles, or rows cut into fewer single units.
-  // It is used when the workspace holds its tables and partial results too; this plan itself
-  // needs no more workspace than the unit, write and merge tables and the single rows'
-  // partials.  Its staging image follows this plan's, and it shares the events.
+  // Its staging image follows this plan's, and it shares the events and the upload lock.
+  // Fine tiles are used when the workspace holds their tables and partial results too.  Those
+  // lie behind this plan's whole workspace, and this plan's tables are uploaded with them
+  // (fine->base), so a call of either form finds its tables whichever ran before.
   std::unique_ptr<Plan> fine;
+  const Plan* base = nullptr;
   // Lengths of a plan whose rows are launched as fewer single units: that form needs no more
   // workspace, so this plan's own tables are never uploaded, and its unit table is built
   // when it is asked for (libra_plan_get_units, guarded by upload_mu).

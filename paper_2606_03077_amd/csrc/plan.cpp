@@ -101,31 +101,46 @@ std::vector<Unit> place_on_slots(const std::vector<Unit>& units, const libra_pla
   return out;
 }
 
-// Places the tables and partial results in the workspace; chunk_slots: partial results of
-// kTileRows rows that the chunk launch writes.
-void workspace_layout(Plan& P, int64_t chunk_slots) {
+size_t place(size_t& off, size_t bytes) {
+  const size_t at = off;
+  off = align256(off + bytes);
+  return at;
+}
+
+// Places the tables and the single rows' partial results in the workspace.
+void workspace_layout(Plan& P) {
   size_t off = 0;
-  auto place = [&off](size_t bytes) {
-    const size_t at = off;
-    off = align256(off + bytes);
-    return at;
-  };
-  P.off_units = place(size_t(P.info.n_units) * kUnitInts * sizeof(int32_t));
-  P.off_writes = place(P.writes.size() * sizeof(int32_t));
-  P.off_merges = place(size_t(P.info.n_merge_groups) * kMergeInts * sizeof(int32_t));
-  P.off_tiles = place(P.tiles.size() * sizeof(int32_t));
-  P.off_chunk_merges = place(P.chunk_merges.size() * sizeof(int32_t));
+  P.off_units = place(off, size_t(P.info.n_units) * kUnitInts * sizeof(int32_t));
+  P.off_writes = place(off, P.writes.size() * sizeof(int32_t));
+  P.off_merges = place(off, size_t(P.info.n_merge_groups) * kMergeInts * sizeof(int32_t));
   P.upload_bytes = off;
   const size_t rows = size_t(P.info.n_partial_slots) * size_t(P.group);
-  P.off_part_o = place(rows * kDim * sizeof(float));
-  P.off_part_lse = place(rows * sizeof(float));
-  const size_t chunk_rows = size_t(chunk_slots) * kTileRows;
-  P.off_chunk_o = place(chunk_rows * kDim * sizeof(float));
-  P.off_chunk_lse = place(chunk_rows * sizeof(float));
+  P.off_part_o = place(off, rows * kDim * sizeof(float));
+  P.off_part_lse = place(off, rows * sizeof(float));
   P.ws_bytes = std::max<size_t>(off, 256);
 }
 
-// A plan of the same batch and tables, whose launch is still to be changed.
+// Places the tables of Q's fine tiles and their chunk_slots partial results (of kTileRows
+// rows) behind the workspace of the plan it is a form of.
+void fine_layout(Plan& Q, const Plan& P, int64_t chunk_slots) {
+  Q.base = &P;
+  Q.off_units = P.off_units;
+  Q.off_writes = P.off_writes;
+  Q.off_merges = P.off_merges;
+  Q.off_part_o = P.off_part_o;
+  Q.off_part_lse = P.off_part_lse;
+  size_t off = P.ws_bytes;
+  Q.upload_off = off;
+  Q.off_tiles = place(off, Q.tiles.size() * sizeof(int32_t));
+  Q.off_chunk_merges = place(off, Q.chunk_merges.size() * sizeof(int32_t));
+  Q.upload_bytes = off - Q.upload_off;
+  const size_t rows = size_t(chunk_slots) * kTileRows;
+  Q.off_chunk_o = place(off, rows * kDim * sizeof(float));
+  Q.off_chunk_lse = place(off, rows * sizeof(float));
+  Q.ws_bytes = off;
+}
+
+// A plan of the same batch, whose tables and launch are still to be set.
 std::unique_ptr<Plan> sibling(const Plan& P) {
   auto Q = std::make_unique<Plan>();
   Q->mode = P.mode;
@@ -135,9 +150,6 @@ std::unique_ptr<Plan> sibling(const Plan& P) {
   Q->group = P.group;
   Q->params = P.params;
   Q->info = P.info;
-  Q->units = P.units;
-  Q->writes = P.writes;
-  Q->merges = P.merges;
   Q->pages_needed = P.pages_needed;
   return Q;
 }
@@ -275,8 +287,7 @@ void build_fine(const std::vector<Unit>& chunks, Plan& P) {
     }
   }
   Q->chunk_grid = kNumXcds * longest_queue;
-  workspace_layout(*Q, slots);
-  Q->ws_bytes = std::max(Q->ws_bytes, P.ws_bytes);
+  fine_layout(*Q, P, slots);
   P.fine = std::move(Q);
 }
 
@@ -603,7 +614,7 @@ libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const
   I.n_merge_groups = int32_t(count_merges(nsplit));
   I.balanced = balanced ? 1 : 0;
 
-  workspace_layout(P, 0);
+  workspace_layout(P);
   build_fine(chunks, P);
   if (fewer) {
     auto Q = sibling(P);
@@ -613,8 +624,9 @@ libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const
     Q->info.n_units = Q->info.n_single = int32_t(Q->units.size() / kUnitInts);
     Q->info.n_partial_slots = int32_t(fewer_slots);
     Q->info.n_merge_groups = int32_t(Q->merges.size() / kMergeInts);
+    Q->writes = P.writes;
     Q->xcd_map = P.xcd_map;
-    workspace_layout(*Q, 0);  // every part is at most as large as P's
+    workspace_layout(*Q);  // every part is at most as large as P's
     Q->ws_bytes = P.ws_bytes;
     P.lens.assign(seq_lens, seq_lens + B);
     P.upload_bytes = 0;

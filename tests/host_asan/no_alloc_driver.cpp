@@ -94,7 +94,7 @@ int main() {
                             it % 2 ? ws2 : ws1, wsb, al16(m.out), m.lse.data(),
                             nullptr) == LIBRA_OK);
   }
-  const FakeHipCounters& after = g_fake_hip;
+  const FakeHipCounters after = g_fake_hip;
   CHECK(after.allocations() == before.allocations());
   CHECK(after.launches > before.launches);          // the calls did reach their launches
   CHECK(after.stream_wait - before.stream_wait == 6);  // fork and join of 3 append calls
@@ -104,6 +104,58 @@ int main() {
   int32_t n_units = 0;
   CHECK(libra_plan_get_units(app, &units, &n_units) == LIBRA_OK && n_units > 0);
   CHECK(std::memcmp(ws2, units, size_t(n_units) * LIBRA_UNIT_INTS * sizeof(int32_t)) == 0);
+
+  CHECK(after.stale_tables == 0);
+
+  // A workspace that holds a plan's tables takes calls of any stated size that the plan
+  // accepts without another copy, and what one form uploads leaves the other's tables
+  // alone, so that a graph captured with either may be replayed after calls of the other.
+  {
+    const int32_t l1[2] = {16001, 900}, c1[2] = {40, 1};
+    libra_plan_desc d1{LIBRA_MODE_APPEND, 2, hq, hkv};
+    libra_plan one = nullptr;
+    CHECK(libra_splitkv_plan(&d1, l1, c1, &p, &one) == LIBRA_OK);
+    libra_plan_info info{};
+    CHECK(libra_plan_get_info(one, &info) == LIBRA_OK && info.n_partial_slots > 0);
+    auto up = [](size_t n) { return (n + 255) / 256 * 256; };
+    const size_t rows1 = size_t(info.n_partial_slots) * (hq / hkv);
+    const size_t plain = up(size_t(info.n_units) * 48) + up(size_t(info.n_write_tiles) * 32) +
+                         up(size_t(info.n_merge_groups) * 32) + up(rows1 * 512) + up(rows1 * 4);
+    const size_t full = libra_plan_workspace_bytes(one);
+    CHECK(full > plain + (1 << 20));                  // the tile's keys are split
+    Buffers w3;
+    unsigned char* ws3 = static_cast<unsigned char*>(w3.ws_aligned(full));
+    const int32_t st1 = 16001 / 16 + 1;
+    std::vector<int32_t> bt1(size_t(2 * st1), 0);
+    Buffers m1;
+    m1.q.assign(size_t(41) * hq * 256 + 16, 0);
+    auto call = [&](size_t bytes) {
+      return libra_append_attn(lay, one, al16(m1.q), al16(m1.q), al16(m1.q), bt1.data(), st1, 2,
+                               hq, 0.088f, ws3, bytes, al16(m1.q), nullptr, nullptr);
+    };
+    auto fine_after = [&](size_t bytes) {             // whether the call takes fine tiles
+      const long n = g_fake_hip.fine_launches;
+      return call(bytes) == LIBRA_OK && g_fake_hip.fine_launches > n;
+    };
+    CHECK(libra_plan_upload(one, ws3, full, nullptr) == LIBRA_OK);
+    const std::vector<unsigned char> held(ws3, ws3 + full);
+    long copies = g_fake_hip.memcpy_async;
+    CHECK(fine_after(full));
+    CHECK(!fine_after(plain));                        // stated too small for the partials
+    CHECK(fine_after(full));
+    CHECK(g_fake_hip.memcpy_async == copies);
+    CHECK(call(plain - 256) == LIBRA_E_WORKSPACE);
+    CHECK(libra_plan_upload(one, ws3, plain, nullptr) == LIBRA_OK);
+    CHECK(std::memcmp(ws3, held.data(), full) == 0);
+    copies = g_fake_hip.memcpy_async;
+    CHECK(!fine_after(full) && !fine_after(plain));   // the plain tables: no copy in a call
+    CHECK(g_fake_hip.memcpy_async == copies);
+    CHECK(libra_plan_upload(one, ws3, full, nullptr) == LIBRA_OK);
+    CHECK(fine_after(full));
+    CHECK(std::memcmp(ws3, held.data(), full) == 0);
+    CHECK(g_fake_hip.stale_tables == 0);
+    libra_plan_destroy(one);
+  }
 
   // Destroying plans frees nothing; a new plan of the same size reuses the pool.
   const FakeHipCounters before_destroy = g_fake_hip;

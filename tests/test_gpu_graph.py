@@ -135,3 +135,41 @@ def test_append_replays_from_a_graph():
     del graph
     cache.close()
     libra.libra_plan_destroy(plan)
+
+
+def test_append_graph_with_split_tiles_survives_calls_in_a_smaller_workspace():
+    """A graph of an append whose tile's keys are split, replayed after eager calls and an
+    upload that state only the workspace of whole tiles."""
+    hq, hkv = 8, 2
+    H.say("[case] graph append, split tiles, smaller stated workspace between replays")
+    b = wl.custom_batch([3072, 700], q_lens=[32, 1], num_q_heads=hq, num_kv_heads=hkv, seed=45)
+    cache = H.DeviceCache(b)
+    plan = H.plan_for(b, num_cus=4)
+    assert H.chunk_partials(plan) >= 2 * hkv
+    ws = libra.alloc_workspace(plan)
+    small = H.plain_workspace(plan)
+    q, kn, vn = H.u16_to_dev(b.q), H.u16_to_dev(b.k_new), H.u16_to_dev(b.v_new)
+    out = torch.empty((33, hq, 128), dtype=torch.int16, device="cuda")
+    lse = torch.empty((33, hq), dtype=torch.float32, device="cuda")
+
+    def call(w):
+        libra.libra_append_attn(cache.layout, plan, q, kn, vn, cache.bt, cache.bt_stride, 2, hq,
+                                b.scale, w, out, lse)
+
+    call(ws)
+    torch.cuda.synchronize()
+    want = out.clone(), lse.clone()
+    graph = _capture(lambda: call(ws))
+    for r in range(REPLAYS):
+        call(ws[:small])
+        if r == 1:
+            libra.libra_plan_upload(plan, ws[:small])
+            call(ws)
+        torch.cuda.synchronize()
+        out.fill_(-1)
+        lse.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert _same_bits(out, want[0]) and _same_bits(lse, want[1]), r
+    libra.libra_plan_destroy(plan)
+    cache.close()
