@@ -45,6 +45,7 @@
 // Skipping the ring's copies past the last key, starting the first copies from scalar page
 // ids and storing whole rows through LDS took 32 prompts of 64-2,048 tokens (40/8 heads)
 // from 860 us to 820 us.
+#include <algorithm>
 #include <cfloat>
 #include <cmath>
 #include <type_traits>
@@ -95,7 +96,9 @@ struct ChunkArgs {
   int hq;
   int group;
   float sl2;
-  int32_t xcd_first[kNumXcds];  // each XCD queue's first tile and tile count
+  int halves;       // narrow form: halves per unit, or 0 where `tiles` holds fine tiles
+  int half_tokens;  // tokens that a unit's first half touches
+  int32_t xcd_first[kNumXcds];  // each XCD queue's first record and workgroup count
   int32_t xcd_count[kNumXcds];
 };
 
@@ -145,7 +148,8 @@ void chunk_kernel(ChunkArgs A) {
   const int xcd = blockIdx.x % kNumXcds;
   const int slot = blockIdx.x / kNumXcds;
   if (slot >= A.xcd_count[xcd]) return;
-  const size_t rec = size_t(A.xcd_first[xcd] + slot);
+  const int shift = !kWide && A.halves == 2 ? 1 : 0;
+  const size_t rec = size_t(A.xcd_first[xcd] + (slot >> shift));
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int col = lane & 31, hh = lane >> 5;  // accumulator column (tile row), lane half
@@ -153,12 +157,21 @@ void chunk_kernel(ChunkArgs A) {
 
   // The workgroup's rows are r_first .. r_first + kRows - 1 of the (token, head) rows of
   // tokens [q0, q1), its keys [kv0, kv1).  The wide form takes a plan unit, the narrow one
-  // a fine tile: half of a unit's rows, and all of its keys or one split of them.
+  // half of a unit's rows: over the keys that they see, straight from the unit's record, or
+  // over one split of them, from a fine tile's.
   int b, g, q0, q1, row0, prior, kv0, kv1, r_first, nsplit, part;
-  if constexpr (kWide) {
+  if (kWide || A.halves) {
     const int32_t* u = A.tiles + rec * kUnitInts;
     b = u[U_B], g = u[U_G], q0 = u[U_Q0], q1 = u[U_Q1], row0 = u[U_ROW0], prior = u[U_PRIOR];
     kv0 = 0, kv1 = u[U_KV1], r_first = 0, nsplit = 1, part = 0;
+    if (!kWide) {
+      if (slot & shift) {
+        r_first = kRows;
+        if (kRows >= (q1 - q0) * G) return;  // no second half
+      } else {
+        kv1 = min(kv1, prior + q0 + A.half_tokens);
+      }
+    }
   } else {
     const int32_t* u = A.tiles + rec * kTileInts;
     b = u[T_B], g = u[T_GH] & 0xFFFF, q0 = u[T_Q0], q1 = u[T_Q1], row0 = u[T_ROW0];
@@ -551,9 +564,11 @@ hipError_t launch_chunk(const KvLayout& L, const Plan& P, void* ws, const void* 
   A.tiles = reinterpret_cast<const int32_t*>(
       w + (P.fine_tiles ? P.off_tiles
                         : P.off_units + size_t(P.info.n_single) * kUnitInts * sizeof(int32_t)));
+  A.halves = P.halves;
+  A.half_tokens = (kTileRows - 1) / P.group + 1;
   for (int x = 0; x < kNumXcds; ++x) {
     A.xcd_first[x] = P.xcd_map[size_t(2 * x)];
-    A.xcd_count[x] = P.xcd_map[size_t(2 * x + 1)];
+    A.xcd_count[x] = P.xcd_map[size_t(2 * x + 1)] * std::max(1, P.halves);
   }
   A.bt = bt;
   A.q = static_cast<const uint16_t*>(q);
@@ -566,7 +581,7 @@ hipError_t launch_chunk(const KvLayout& L, const Plan& P, void* ws, const void* 
   A.hq = P.num_q_heads;
   A.group = P.group;
   A.sl2 = scale * kLog2e;
-  if (P.fine_tiles)
+  if (P.fine_tiles || P.halves)
     hipLaunchKernelGGL(chunk_kernel<kNarrowWaves>, dim3(unsigned(P.chunk_grid)),
                        dim3(64 * kNarrowWaves), 0, s, A);
   else

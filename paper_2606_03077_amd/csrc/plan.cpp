@@ -154,9 +154,13 @@ std::unique_ptr<Plan> sibling(const Plan& P) {
   return Q;
 }
 
-// Builds P.fine, the plan whose chunk launch takes fine tiles (kTileRows rows each, four
-// waves, two workgroups per CU) where that is faster than the chunk units on workgroups of
-// kChunkRows rows (eight waves, one per CU).  chunks: the chunk units in queue order.
+// Chooses the form of the chunk launch: chunk units on workgroups of kChunkRows rows (eight
+// waves, one per CU), or fine tiles of kTileRows rows (four waves, two workgroups per CU)
+// where that is faster.  Whole fine tiles in many waves are the halves of the units, in their
+// queues' order, and need no table of their own (P.halves); those of a single wave, whose keys
+// may be split, get one (P.fine).  Built without a table of many thousand tiles, a plan costs
+// the host what one of units does (32 prompts of 64-2,048 tokens 149 us, with it 310 us).
+// longest_queue: units of the longest queue.
 //
 // At most S = 2 num_cus fine tiles are resident at once and their longest sets the launch's
 // time, so their keys may be split as well: into ceil(steps / t) near-equal ranges, t being
@@ -177,116 +181,142 @@ std::unique_ptr<Plan> sibling(const Plan& P) {
 constexpr int64_t kMinPieceSteps = 8;
 constexpr int64_t kMaxFineSlots = 2048;  // bounds the partial results (64.5 KiB each)
 
-void build_fine(const std::vector<Unit>& chunks, Plan& P) {
-  struct Tile { int64_t unit, h, keys, steps, part; };
-  const int64_t cus = P.params.num_cus;
-  const int64_t S = std::min<int64_t>(2 * cus, kMaxFineSlots);
-  std::vector<Tile> tiles;
-  int64_t longest = 0, total = 0, longest_unit = 0, wide_cost = 0;
-  for (size_t i = 0; i < chunks.size(); ++i) {
-    const Unit& u = chunks[i];
-    const int64_t unit_steps = ceil_div(u[U_KV1], kChunkStepKeys);
-    longest_unit = std::max(longest_unit, unit_steps);
-    wide_cost += 167 * unit_steps + 840;
-    for (int64_t h = 0; h * kTileRows < (u[U_Q1] - u[U_Q0]) * int64_t(P.group); ++h) {
-      const int64_t tokens = std::min<int64_t>(
-          u[U_Q1], u[U_Q0] + (h * kTileRows + kTileRows - 1) / P.group + 1);
-      const int64_t keys = u[U_PRIOR] + tokens, steps = ceil_div(keys, kTileStepKeys);
-      tiles.push_back({int64_t(i), h, keys, steps, -1});
-      longest = std::max(longest, steps);
-      total += steps;
-    }
+// A row of an append with its tokens and KV length before them; its chunk units and their
+// halves are the same for every KV head.
+struct ChunkRow { int64_t b, tokens, prior, row0; };
+// Half h (rows [128 h, 128 h + 128)) of the unit of tokens [q0, q1): it sees `keys` keys,
+// cut into n pieces (set, with the pieces' running partial slot and step, as they are cut).
+struct Tile { int64_t q0, q1, h, keys, steps, n, slot, step; };
+
+// Calls f(tile, first half of its unit) on the halves of a chunk row's units.
+template <class F>
+void each_tile(const ChunkRow& r, int64_t T, int64_t G, F f) {
+  const int64_t half = (kTileRows - 1) / G + 1;  // tokens that a unit's first half touches
+  for (int64_t q0 = 0; q0 < r.tokens; q0 += T) {
+    const int64_t q1 = std::min(q0 + T, r.tokens);
+    const int64_t k0 = r.prior + std::min(q1, q0 + half), k1 = r.prior + q1;
+    f(Tile{q0, q1, 0, k0, ceil_div(k0, kTileStepKeys), 1, -1, 0});
+    if ((q1 - q0) * G > kTileRows) f(Tile{q0, q1, 1, k1, ceil_div(k1, kTileStepKeys), 1, -1, 0});
   }
-  const int64_t n = int64_t(tiles.size()), units = int64_t(chunks.size());
+}
+
+void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t longest_queue, Plan& P) {
+  const int64_t cus = P.params.num_cus, Hkv = P.num_kv_heads, G = P.group;
+  const int64_t S = std::min<int64_t>(2 * cus, kMaxFineSlots);
+  int64_t n = 0, units = 0, longest = 0, total = 0, longest_unit = 0, wide_cost = 0, halves = 1;
+  for (const ChunkRow& r : rows) {
+    each_tile(r, T, G, [&](const Tile& t) {
+      n += Hkv;
+      longest = std::max(longest, t.steps);
+      total += Hkv * t.steps;
+      if (t.h) {
+        halves = 2;
+        return;
+      }
+      const int64_t unit_steps = ceil_div(r.prior + t.q1, kChunkStepKeys);
+      units += Hkv;
+      longest_unit = std::max(longest_unit, unit_steps);
+      wide_cost += Hkv * (167 * unit_steps + 840);
+    });
+  }
   if (n == 0) return;
-  const bool one_wave = n <= S;
-  int64_t piece = longest;
-  if (one_wave) {
-    auto pieces = [&](int64_t t) {
-      int64_t k = 0;
-      for (const Tile& x : tiles) k += ceil_div(x.steps, t);
-      return k;
-    };
-    int64_t t = std::min(kMinPieceSteps, longest), hi = longest;
-    while (t < hi) {
-      const int64_t mid = (t + hi) / 2;
-      if (pieces(mid) <= S) hi = mid;
-      else t = mid + 1;
+  if (n > S) {
+    if (wide_cost > 46 * total + 330 * n) {  // the units' queues and tables serve as they are
+      P.halves = int32_t(halves);
+      P.chunk_grid = kNumXcds * longest_queue * halves;
     }
-    const int64_t whole_time = longest * (n <= cus ? 65 : 93) + 700;
-    const int64_t split_time = t * (pieces(t) <= cus ? 65 : 93) + 2000;
-    if (split_time < whole_time) piece = t;
-    const int64_t wide_step = std::max<int64_t>(125, 80 + 90 * units / cus);
-    if (units <= cus && longest_unit * wide_step + 800 < std::min(whole_time, split_time)) return;
-  } else if (wide_cost <= 46 * total + 330 * n) {
     return;
   }
 
+  // One wave: the tiles' keys may be split.
+  std::vector<Tile> tiles;  // of one KV head
+  std::vector<size_t> row_end;
+  tiles.reserve(size_t(n / Hkv));
+  for (const ChunkRow& r : rows) {
+    each_tile(r, T, G, [&](const Tile& t) { tiles.push_back(t); });
+    row_end.push_back(tiles.size());
+  }
+  auto pieces = [&](int64_t t) {
+    int64_t k = 0;
+    for (const Tile& x : tiles) k += ceil_div(x.steps, t);
+    return k * Hkv;
+  };
+  int64_t piece = longest, t = std::min(kMinPieceSteps, longest);
+  for (int64_t hi = longest; t < hi;) {
+    const int64_t mid = (t + hi) / 2;
+    if (pieces(mid) <= S) hi = mid;
+    else t = mid + 1;
+  }
+  const int64_t whole_time = longest * (n <= cus ? 65 : 93) + 700;
+  const int64_t split_time = t * (pieces(t) <= cus ? 65 : 93) + 2000;
+  if (split_time < whole_time) piece = t;
+  const int64_t wide_step = std::max<int64_t>(125, 80 + 90 * units / cus);
+  if (units <= cus && longest_unit * wide_step + 800 < std::min(whole_time, split_time)) return;
+
+  // Pieces that read the same keys next to each other (by row, KV head and key range), the
+  // list cut into eight runs of equal cost, one per XCD, so that they share an L2; each
+  // queue its longest piece first.
   auto Q = sibling(P);
   Q->fine_tiles = true;
-  int64_t slots = 0;
-  for (Tile& t : tiles) {
-    const int64_t k = ceil_div(t.steps, piece);
-    if (k == 1) continue;
-    const Unit& u = chunks[size_t(t.unit)];
-    t.part = slots;
-    slots += k;
-    const int32_t rec[kMergeInts] = {int32_t(u[U_G] | t.h << 16), u[U_Q0], int32_t(k),
-                                     int32_t(t.part), u[U_ROW0], u[U_Q1], 0, 0};
-    Q->chunk_merges.insert(Q->chunk_merges.end(), rec, rec + kMergeInts);
-  }
-  struct Piece { const Tile* tile; int64_t j, steps; };
+  struct Piece { int32_t rec[kTileInts]; int64_t steps; };
   std::vector<std::vector<Piece>> queues(kNumXcds);
-  if (!one_wave) {  // the units' queues, a unit's tiles next to each other: they read the same keys
-    for (const Tile& t : tiles) {
-      int x = 0;
-      while (t.unit >= P.xcd_map[size_t(2 * x)] + P.xcd_map[size_t(2 * x + 1)]) ++x;
-      queues[size_t(x)].push_back({&t, 0, t.steps});
+  for (auto& q : queues) q.reserve(size_t(S / kNumXcds + 1));
+  int64_t slots = 0, before = 0, x = 0;
+  for (Tile& t : tiles) t.n = ceil_div(t.steps, piece);
+  for (size_t i = 0; i < rows.size(); ++i) {
+    const ChunkRow& r = rows[i];
+    Tile* const first = tiles.data() + (i ? row_end[i - 1] : 0);
+    Tile* const last = tiles.data() + row_end[i];
+    int64_t most = 1;
+    for (const Tile* t = first; t < last; ++t) most = std::max(most, t->n);
+    for (int64_t g = 0; g < Hkv; ++g) {
+      for (Tile* t = first; t < last; ++t) {
+        t->step = 0;
+        if (t->n == 1) continue;
+        const int32_t rec[kMergeInts] = {int32_t(g | t->h << 16), int32_t(t->q0), int32_t(t->n),
+                                         int32_t(slots), int32_t(r.row0), int32_t(t->q1), 0, 0};
+        Q->chunk_merges.insert(Q->chunk_merges.end(), rec, rec + kMergeInts);
+        t->slot = slots;
+        slots += t->n;
+      }
+      for (int64_t j = 0; j < most; ++j) {
+        for (Tile* t = first; t < last; ++t) {
+          if (j >= t->n) continue;
+          const int64_t s0 = t->step, s1 = (j + 1) * t->steps / t->n;
+          t->step = s1;
+          // the eighth of the total that the middle of the piece lies in
+          while ((2 * before + s1 - s0) * kNumXcds >= 2 * total * (x + 1)) ++x;
+          before += s1 - s0;
+          queues[size_t(x)].push_back(
+              {{int32_t(r.b), int32_t(g | t->h << 16), int32_t(t->q0), int32_t(t->q1),
+                int32_t(r.row0), int32_t(r.prior), int32_t(s0 * kTileStepKeys),
+                int32_t(std::min(s1 * kTileStepKeys, t->keys)),
+                t->n > 1 ? int32_t(t->slot + j) : -1, int32_t(t->n)}, s1 - s0});
+        }
+      }
     }
-  } else {
-    // Pieces that read the same keys next to each other, the list cut into eight runs of
-    // equal cost, one per XCD, so that they share an L2; each queue its longest piece first.
-    std::vector<Piece> all;
-    for (const Tile& t : tiles) {
-      const int64_t k = ceil_div(t.steps, piece);
-      for (int64_t j = 0; j < k; ++j)
-        all.push_back({&t, j, (j + 1) * t.steps / k - j * t.steps / k});
-    }
-    std::sort(all.begin(), all.end(), [&](const Piece& x, const Piece& y) {
-      const Unit &a = chunks[size_t(x.tile->unit)], &b = chunks[size_t(y.tile->unit)];
-      if (a[U_B] != b[U_B]) return a[U_B] < b[U_B];
-      if (a[U_G] != b[U_G]) return a[U_G] < b[U_G];
-      if (x.j != y.j) return x.j < y.j;
-      if (a[U_Q0] != b[U_Q0]) return a[U_Q0] < b[U_Q0];
-      return x.tile->h < y.tile->h;
-    });
-    int64_t before = 0;
-    for (const Piece& p : all) {
-      queues[size_t((2 * before + p.steps) * kNumXcds / (2 * total))].push_back(p);
-      before += p.steps;
-    }
-    for (auto& q : queues)
-      std::stable_sort(q.begin(), q.end(),
-                       [](const Piece& a, const Piece& b) { return a.steps > b.steps; });
   }
-  int64_t longest_queue = 0;
+  size_t all = 0, done = 0, longest_run = 0;
+  for (const auto& q : queues) all += q.size();
+  Q->tiles.resize(all * kTileInts);
   for (const auto& q : queues) {
-    Q->xcd_map.push_back(int32_t(Q->tiles.size() / kTileInts));
+    Q->xcd_map.push_back(int32_t(done));
     Q->xcd_map.push_back(int32_t(q.size()));
-    longest_queue = std::max(longest_queue, int64_t(q.size()));
-    for (const Piece& p : q) {
-      const Tile& t = *p.tile;
-      const Unit& u = chunks[size_t(t.unit)];
-      const int64_t k = ceil_div(t.steps, piece);
-      const int64_t kv0 = p.j * t.steps / k * kTileStepKeys;
-      const int64_t kv1 = std::min((p.j + 1) * t.steps / k * kTileStepKeys, t.keys);
-      const int32_t rec[kTileInts] = {u[U_B], int32_t(u[U_G] | t.h << 16), u[U_Q0], u[U_Q1],
-                                      u[U_ROW0], u[U_PRIOR], int32_t(kv0), int32_t(kv1),
-                                      k > 1 ? int32_t(t.part + p.j) : -1, int32_t(k)};
-      Q->tiles.insert(Q->tiles.end(), rec, rec + kTileInts);
-    }
+    longest_run = std::max(longest_run, q.size());
+    // In order of 64 buckets of length: sizes differ by a step or two where keys are cut.
+    int64_t most = 0, least = INT64_MAX;
+    for (const Piece& p : q) most = std::max(most, p.steps), least = std::min(least, p.steps);
+    int shift = 0;
+    while (!q.empty() && (most - least) >> shift > 63) ++shift;
+    std::array<size_t, 65> at{};
+    for (const Piece& p : q) ++at[size_t((most - p.steps) >> shift) + 1];
+    for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
+    for (const Piece& p : q)
+      std::memcpy(Q->tiles.data() + (done + at[size_t((most - p.steps) >> shift)]++) * kTileInts, p.rec,
+                  sizeof(p.rec));
+    done += q.size();
   }
-  Q->chunk_grid = kNumXcds * longest_queue;
+  Q->chunk_grid = kNumXcds * int64_t(longest_run);
   fine_layout(*Q, P, slots);
   P.fine = std::move(Q);
 }
@@ -430,12 +460,14 @@ libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const
   if (!fewer)
     singles = single_units(nsplit, slot_base, balanced ? int64_t(p.num_cus) : int64_t(kNumXcds));
   std::vector<Unit> chunks;
+  std::vector<ChunkRow> chunk_rows;
 
   // Step 7: query tiles of chunk rows.
   const int64_t T = p.q_tile > 0 ? p.q_tile : int64_t(kChunkRows) / G;
   for (int64_t b = 0; b < B; ++b) {
     if (C[b] == 1) continue;
     const int64_t P = L[b] - C[b];
+    chunk_rows.push_back({b, C[b], P, row0[b]});
     for (int64_t g = 0; g < Hkv; ++g) {
       for (int64_t q0 = 0; q0 < C[b]; q0 += T) {
         const int64_t q1 = std::min(q0 + T, C[b]);
@@ -578,6 +610,7 @@ libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const
 
   P.xcd_map.assign(xcd_map, xcd_map + 2 * kNumXcds);
   P.chunk_grid = int64_t(kNumXcds) * longest;
+  P.halves = 0;
 
   // Split-merge table: every single row with n_b > 1, per KV head, ascending (b, g).
   auto merge_table = [&](const std::vector<int64_t>& n, const std::vector<int64_t>& base) {
@@ -615,7 +648,7 @@ libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const
   I.balanced = balanced ? 1 : 0;
 
   workspace_layout(P);
-  build_fine(chunks, P);
+  build_fine(chunk_rows, T, longest, P);
   if (fewer) {
     auto Q = sibling(P);
     for (const Unit& u : single_units(fewer->n, fewer_base, cus))

@@ -26,7 +26,8 @@ constexpr int kChunkRows = 256;  // most (token, head) rows of one query tile
 constexpr int kTileRows = 128;   // rows of a fine tile: a query tile is one or two of them
 constexpr int kTileStepKeys = 32;  // keys per step of the chunk kernel on fine tiles
 
-// Fine tiles: one record per workgroup of the chunk kernel's narrow form.  It takes rows
+// Fine tiles: one record per workgroup of the chunk kernel's narrow form where they fit in one
+// wave (whole tiles in many waves are taken from the unit table).  A workgroup takes rows
 // [128 h, 128 h + 128) of the query tile [q0, q1) of (sequence b, KV head g), T_GH =
 // g | h << 16, over keys [kv0, kv1): all of them, or split `part` of n.
 enum TileField : int { T_B = 0, T_GH, T_Q0, T_Q1, T_ROW0, T_PRIOR, T_KV0, T_KV1, T_PART, T_NSPLIT };
