@@ -1,16 +1,18 @@
 // Log-sum-exp merge of split rows: the float32 partials that decode units wrote for
 // the pieces of one (sequence, KV head) row become its bf16 output and float32 LSE.
 //
-// One 256-thread block per query head of a split row: 16 groups of 16 threads, thread t of a
-// group channels 8 t .. + 7.  Group k folds splits k, k + 16, ... four at a time (all loads
-// of a batch in flight) with a running maximum, so up to 64 splits take one round of loads;
-// the groups' (max, sum, accumulator) then combine by lane shuffles within a wave and
-// through LDS across the four waves, in a fixed order.  With M = max_j lse_j (base 2): lse =
-// M + log2(sum_j 2^(lse_j - M)), o = sum_j 2^(lse_j - lse) o_j; empty splits (lse_j = -inf)
-// add nothing.  Bound by latency (record, one round of loads, combine, store),
-// so splits are spread over the block rather than looped over: with one block per row, whose
-// threads looped over the splits, a lone 40,960-token decode (8 rows of 64 splits) took 33.1
-// us, now 31.2 us; a 28-layer step of 16 requests 765 us, now 750 us.
+// One 256-thread block per query head of a split row: up to 16 groups of 16 threads, thread t
+// of a group channels 8 t .. + 7.  Group k folds splits k, k + groups, ... four at a time
+// (all loads of a batch in flight) with a running maximum, so up to 64 splits take one round
+// of loads; the groups' (max, sum, accumulator) then combine by lane shuffles within a wave
+// and through LDS across the four waves, in a fixed order.  With M = max_j lse_j (base 2):
+// lse = M + log2(sum_j 2^(lse_j - M)), o = sum_j 2^(lse_j - lse) o_j; empty splits
+// (lse_j = -inf) add nothing.  Bound by latency (record, one round of loads, combine, store),
+// so splits are spread over the block rather than looped over, and a row of at most 16 splits
+// uses one wave, one of at most four a single group.  Kernel time for two rows of two splits
+// (8 heads): 2.7 us with a block per row whose threads looped over the splits, 3.2 with 16
+// groups for every row, 2.5 now; for the 8 rows of a 40,960-token request (40 heads) 5.1 us
+// in 64 splits, and in the 32 that are launched since 4.6 and 4.5 us.
 #include <algorithm>
 #include <cmath>
 
@@ -49,10 +51,14 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(MergeArgs A) {
   __shared__ __align__(16) float red_acc[kWaves][16][12];  // padded row
 
   const int G = A.group;
-  const int32_t* m = A.merges + size_t(blockIdx.x / unsigned(G)) * kMergeInts;
-  const int h = blockIdx.x % unsigned(G);
+  const int32_t* m = A.merges + size_t(blockIdx.x) * kMergeInts;
+  const int h = blockIdx.y;
   const int g = m[M_G], n = m[M_N], part = m[M_PART], row = m[M_ROW];
   const int tid = threadIdx.x, t = tid & 15, grp = tid >> 4;
+  // Few splits: as many groups as one batch of loads each needs, and only the rounds of the
+  // combine that these take.  Uniform over the block.
+  const int groups = n <= kRowBatch ? 1 : n <= kRowBatch * 4 ? 4 : kGroups;
+  if (grp >= groups) return;
 
   float M = -INFINITY, wsum = 0.f;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -66,12 +72,12 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(MergeArgs A) {
     for (int i = 0; i < 8; ++i) acc[i] = acc[i] * a + xk[i] * b;
     M = Mn;
   };
-  for (int j0 = grp; j0 < n; j0 += kRowBatch * kGroups) {
+  for (int j0 = grp; j0 < n; j0 += kRowBatch * groups) {
     float lj[kRowBatch];
     f32x4 x0[kRowBatch], x1[kRowBatch];
 #pragma unroll
     for (int jj = 0; jj < kRowBatch; ++jj) {
-      const int j = j0 + jj * kGroups;
+      const int j = j0 + jj * groups;
       lj[jj] = -INFINITY;
       x0[jj] = x1[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
       if (j < n) {
@@ -102,30 +108,36 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(MergeArgs A) {
     }
     M = Mc;
   }
+  if (groups > 1) {
 #pragma unroll
-  for (int d = 16; d < 64; d *= 2) {
-    float x[8];
+    for (int d = 16; d < 64; d *= 2) {
+      float x[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = __shfl_xor(acc[i], d);
-    const float Mk = __shfl_xor(M, d), wk = __shfl_xor(wsum, d);
-    fold(Mk, wk, x);
+      for (int i = 0; i < 8; ++i) x[i] = __shfl_xor(acc[i], d);
+      const float Mk = __shfl_xor(M, d), wk = __shfl_xor(wsum, d);
+      fold(Mk, wk, x);
+    }
   }
-  const int wave = tid >> 6;
-  if ((tid & 63) < 16) {
-    red_m[wave][t] = M;
-    red_w[wave][t] = wsum;
+  if (groups > 4) {
+    const int wave = tid >> 6;
+    if ((tid & 63) < 16) {
+      red_m[wave][t] = M;
+      red_w[wave][t] = wsum;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) red_acc[wave][t][i] = acc[i];
+      for (int i = 0; i < 8; ++i) red_acc[wave][t][i] = acc[i];
+    }
+    __syncthreads();
+    if (tid < 16) {
+#pragma unroll
+      for (int k = 1; k < kWaves; ++k) {
+        float x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = red_acc[k][t][i];
+        fold(red_m[k][t], red_w[k][t], x);
+      }
+    }
   }
-  __syncthreads();
   if (tid >= 16) return;
-#pragma unroll
-  for (int k = 1; k < kWaves; ++k) {
-    float x[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = red_acc[k][t][i];
-    fold(red_m[k][t], red_w[k][t], x);
-  }
   const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
   uint4 ov;
   ov.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
@@ -236,13 +248,13 @@ hipError_t launch_merge(const Plan& P, void* ws, void* out, float* lse, hipStrea
   A.lse = lse;
   A.hq = P.num_q_heads;
   A.group = P.group;
-  // One block per (record, head); a 1-D grid holds at most 2^32 - 1 work-items.
+  // Blocks (record, head); a grid's dimension holds at most 2^32 - 1 work-items.
   const int32_t* const first = A.merges;
-  const int most = int((int64_t(1) << 23) / P.group);
-  for (int r0 = 0; r0 < n; r0 += most) {
+  constexpr int kMost = 1 << 23;
+  for (int r0 = 0; r0 < n; r0 += kMost) {
     A.merges = first + size_t(r0) * kMergeInts;
-    const unsigned blocks = unsigned(std::min(most, n - r0)) * unsigned(P.group);
-    hipLaunchKernelGGL(merge_kernel, dim3(blocks), dim3(kThreads), 0, s, A);
+    hipLaunchKernelGGL(merge_kernel, dim3(unsigned(std::min(kMost, n - r0)), unsigned(P.group)),
+                       dim3(kThreads), 0, s, A);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -13,6 +13,7 @@ import numpy as np
 import pytest
 
 import oracle
+from paper_2606_03077_amd import libra
 from paper_2606_03077_amd import workloads as wl
 
 import gpu_harness as H
@@ -71,3 +72,24 @@ def test_decode_with_moving_maximum(rising):
     ro, rl = oracle.decode_ref(b.q, b.k_pages, b.v_pages, b.block_table, b.seq_lens, b.scale)
     H.assert_parity(o, lse, ro, rl, label=f"decode moving max rising={rising}")
     cache.close()
+
+
+@pytest.mark.parametrize("rising", [True, False])
+@pytest.mark.parametrize("group", [1, 5, 16])
+def test_merge_at_the_edges_of_its_groups_and_rounds(group, rising):
+    """Rows of 1 to 128 splits: a single group of the merge's block, one wave, the whole block,
+    and a second round of loads (beyond 64), whose maxima lie above or below the first's."""
+    splits = [1, 2, 4, 5, 16, 17, 63, 64, 65, 80, 128]
+    lens = [16 * n - 3 for n in splits[:-1]] + [16 * 200]
+    H.say(f"[case] merge G={group} splits={splits} rising={rising}")
+    b = wl.custom_batch(lens, num_q_heads=2 * group, num_kv_heads=2, seed=79)
+    _scale_keys(b, rising)
+    params = dict(num_cus=4096, units_per_cu=1, min_split_pages=1, max_splits=128)
+    plan = H.plan_for(b, **params)
+    units = libra.libra_plan_get_units(plan)
+    libra.libra_plan_destroy(plan)
+    assert [int(units[units[:, 0] == i, 7][0]) for i in range(len(lens))] == splits
+    o, lse, cache, _ = H.run(b, plan_params=params)
+    cache.close()
+    ro, rl = oracle.decode_ref(b.q, b.k_pages, b.v_pages, b.block_table, b.seq_lens, b.scale)
+    H.assert_parity(o, lse, ro, rl, label=f"merge edges G={group} rising={rising}")
