@@ -160,7 +160,8 @@ std::unique_ptr<Plan> sibling(const Plan& P) {
 // queues' order, and need no table of their own (P.halves); those of a single wave, whose keys
 // may be split, get one (P.fine).  Built without a table of many thousand tiles, a plan costs
 // the host what one of units does (32 prompts of 64-2,048 tokens 149 us, with it 310 us).
-// longest_queue: units of the longest queue.
+// single_pages: pages of the decode rows beside them, over the KV heads; longest_queue: units
+// of the longest queue.
 //
 // At most S = 2 num_cus fine tiles are resident at once and their longest sets the launch's
 // time, so their keys may be split as well: into ceil(steps / t) near-equal ranges, t being
@@ -178,6 +179,17 @@ std::unique_ptr<Plan> sibling(const Plan& P) {
 // 64 x 100 tokens on 500 78 and 81 us), query tiles of at most 128 rows (128 x 20 tokens on
 // 2,000, 4 heads per KV head: 218 and 266 us) and launches that leave CUs idle (333 tokens on
 // 16,001: 129 and 326 us; 800 on 16,000: 267 and 340 us; 4 x 8 on 30,000: 54 and 583 us).
+// Decode rows run beside the chunk launch, which is dispatched first: they take about 330 ns
+// per page of a CU, start some 12 us later (the fork) and find the share of the CUs that the
+// chunk workgroups leave, so a form ends after max(t, 12 us + decode + t * share it fills); a
+// fine tile shares its CU with them (0.93 us a step), a wide workgroup's LDS keeps them off.
+// Tiles cut to fill the chip then only pay where whole units would outlast the decode rows,
+// and units are taken up to 5% above, as their CUs serve the decode rows' last wave better.
+// Measured with 32 heads on 8 KV heads, cut tiles and units: 333 tokens on 4,000 alone 45 and
+// 94 us, beside 16 rows of 1,000 78 and 107 us, beside 127 of them 149 and 121 us; on 16,000
+// beside 127 of 1,000 206 and 335 us, of 4,000 441 and 379 us (whole tiles 411 us); 20 tokens
+// on 430 beside 16 rows of 16,000 206 us as whole tiles, 189 us as units; 8 x 300 on 500 (more
+// than a wave) beside 16 rows of 16,000 243 and 235 us.
 constexpr int64_t kMinPieceSteps = 8;
 constexpr int64_t kMaxFineSlots = 2048;  // bounds the partial results (64.5 KiB each)
 
@@ -200,7 +212,8 @@ void each_tile(const ChunkRow& r, int64_t T, int64_t G, F f) {
   }
 }
 
-void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t longest_queue, Plan& P) {
+void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t single_pages,
+                int64_t longest_queue, Plan& P) {
   const int64_t cus = P.params.num_cus, Hkv = P.num_kv_heads, G = P.group;
   const int64_t S = std::min<int64_t>(2 * cus, kMaxFineSlots);
   int64_t n = 0, units = 0, longest = 0, total = 0, longest_unit = 0, wide_cost = 0, halves = 1;
@@ -220,8 +233,9 @@ void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t longest_qu
     });
   }
   if (n == 0) return;
+  const int64_t bias = single_pages ? 95 : 100;  // of the units' time, beside decode rows
   if (n > S) {
-    if (wide_cost > 46 * total + 330 * n) {  // the units' queues and tables serve as they are
+    if (wide_cost * bias > 100 * (46 * total + 330 * n)) {  // the units' queues and tables serve as they are
       P.halves = int32_t(halves);
       P.chunk_grid = kNumXcds * longest_queue * halves;
     }
@@ -247,11 +261,19 @@ void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t longest_qu
     if (pieces(mid) <= S) hi = mid;
     else t = mid + 1;
   }
-  const int64_t whole_time = longest * (n <= cus ? 65 : 93) + 700;
-  const int64_t split_time = t * (pieces(t) <= cus ? 65 : 93) + 2000;
+  const int64_t single_time = 33 * single_pages / cus;
+  auto beside = [&](int64_t time, int64_t groups, int64_t room) {
+    if (single_pages == 0) return time;
+    return std::max(time, 1200 + single_time + time * std::min(groups, room) / room);
+  };
+  auto step = [&](int64_t groups) { return groups <= cus && single_pages == 0 ? 65 : 93; };
+  const int64_t cut = pieces(t);
+  const int64_t whole_time = beside(longest * step(n) + 700, n, 2 * cus);
+  const int64_t split_time = beside(t * step(cut) + 2000, cut, 2 * cus);
   if (split_time < whole_time) piece = t;
   const int64_t wide_step = std::max<int64_t>(125, 80 + 90 * units / cus);
-  if (units <= cus && longest_unit * wide_step + 800 < std::min(whole_time, split_time)) return;
+  const int64_t wide_time = beside(longest_unit * wide_step + 800, units, cus);
+  if (units <= cus && wide_time * bias < 100 * std::min(whole_time, split_time)) return;
 
   // Pieces that read the same keys next to each other (by row, KV head and key range), the
   // list cut into eight runs of equal cost, one per XCD, so that they share an L2; each
@@ -648,7 +670,7 @@ libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const
   I.balanced = balanced ? 1 : 0;
 
   workspace_layout(P);
-  build_fine(chunk_rows, T, longest, P);
+  build_fine(chunk_rows, T, W, longest, P);
   if (fewer) {
     auto Q = sibling(P);
     for (const Unit& u : single_units(fewer->n, fewer_base, cus))

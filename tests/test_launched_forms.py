@@ -75,3 +75,18 @@ def test_whole_tiles_in_many_waves_have_no_table(driver):
     short, long = forms(driver, [line(prompts, prompts, 40, 8), line([40960], [40960], 40, 8)])
     assert short["form"] == "halves" and short["workspace"] == short["plain"]
     assert long["form"] == "units" and long["workspace"] == long["plain"]
+
+
+def test_chunk_tiles_are_not_cut_where_decode_rows_fill_the_chip(driver):
+    """Cutting a chunk's keys over all CUs delays the decode rows beside it, so it is done only
+    where whole units would outlast them."""
+    def form(chunks, tokens, prior, rows, length):
+        lens = [prior + tokens] * chunks + [length] * rows
+        return line(lens, [tokens] * chunks + [1] * rows, 32, 8)
+
+    cases = [(1, 333, 4000, 0, 0, True), (1, 333, 4000, 16, 1000, True),
+             (1, 333, 4000, 127, 1000, False), (1, 333, 16000, 127, 1000, True),
+             (1, 333, 16000, 127, 4000, False), (1, 500, 4000, 16, 16000, False),
+             (4, 64, 4000, 127, 1000, False), (4, 64, 16000, 16, 16000, True)]
+    got = forms(driver, [form(*c[:5]) for c in cases])
+    assert [f["parts"] > 1 for f in got] == [c[5] for c in cases]
