@@ -1,10 +1,13 @@
 """Append tiles cut by rows and keys: the forms of the chunk launch against the oracle.
 
-Few chunk tiles run as 128-row workgroups whose keys may be split, with the partials merged;
-many full ones as whole 256-row tiles.  The cases sit at the edges: rows of one head group at
-and beside 128 and 256, key counts at and beside the 32-key step and the smallest piece, rows
-that see no key of a split, one-token tails, and the workspace that is too small for the
-partials (the same results, unsplit)."""
+Few chunk tiles run as 128-row workgroups whose keys may be split, with the partials merged
+("tiles"); short or half-filled ones in many waves as halves of their units ("halves"); many
+long full ones, or those beside decode rows that fill the chip, as whole 256-row tiles
+("units").  The cases sit at the edges: rows of one head group at and beside 128 and 256, key
+counts at and beside the 32-key step and the smallest piece, rows that see no key of a split,
+one-token tails, more pages than the staged block-table row holds, and the workspace that is
+too small for the partials (the same results, unsplit).  The planner's form for each, and the
+most key ranges of a tile, are asserted by a host test."""
 import numpy as np
 import pytest
 import torch
@@ -17,26 +20,32 @@ import gpu_harness as H
 
 pytestmark = pytest.mark.gpu
 
-# (KV lengths after the append, new tokens, query heads, KV heads, CUs)
+# (KV lengths after the append, new tokens, query heads, KV heads, CUs, form, key ranges)
 CASES = [
-    ([33], [2], 4, 1, 256),                       # two tokens, one step past a boundary
-    ([1056, 1025], [32, 32], 4, 1, 256),          # 128 rows exactly; 33 and 32.03 steps
-    ([1500], [33], 4, 1, 256),                    # 132 rows: a second tile of four rows
-    ([2100], [2], 16, 1, 256),                    # 32 rows, many pieces of the minimum size
-    ([4000, 17, 900], [51, 17, 40], 10, 2, 64),   # 255 rows; a prefill; a short tile
-    ([700, 3000, 64], [300, 1, 64], 14, 2, 64),   # decode rows beside chunk tiles
-    ([900], [850], 8, 8, 256),                    # rows that see no key of the later splits
-    ([6000], [90], 16, 1, 8),                     # 16-head groups, few slots
-    ([130] * 12, [130] * 12, 8, 1, 2),            # more full tiles than slots: whole tiles
-    ([400] * 9, [20] * 9, 8, 2, 4),               # many waves of half-filled tiles
-    ([66000], [40], 4, 1, 256),                   # past the staged block-table row
+    ([33], [2], 4, 1, 256, "tiles", 1),               # two tokens, one step past a boundary
+    ([1056, 1025], [32, 32], 4, 1, 256, "tiles", 5),  # 128 rows exactly; 33 and 32.03 steps
+    ([1500], [33], 4, 1, 256, "tiles", 6),            # 132 rows: a second tile of four rows
+    ([2100], [2], 16, 1, 256, "tiles", 9),            # 32 rows, pieces of the minimum size
+    ([4000, 17, 900], [51, 17, 40], 10, 2, 64, "tiles", 16),  # 255 rows; a prefill; short tiles
+    ([2700, 300, 3064], [300, 1, 64], 14, 2, 256, "tiles", 12),  # a decode row beside chunk tiles
+    ([700, 3000, 64], [300, 1, 64], 14, 2, 64, "units", 1),  # and one that outlasts them
+    ([900], [850], 8, 8, 256, "tiles", 4),            # rows that see no key of the later splits
+    ([6000], [10], 16, 1, 8, "tiles", 8),             # 16-head groups, few slots
+    ([6000], [90], 16, 1, 8, "units", 1),             # and enough tiles of them for whole units
+    ([130] * 12, [130] * 12, 8, 1, 2, "halves", 1),   # more full tiles than slots
+    ([400] * 9, [20] * 9, 8, 2, 4, "halves", 1),      # many waves of half-filled tiles
+    ([700] * 5, [37] * 5, 14, 2, 4, "halves", 1),     # and of second halves of few rows
+    ([3000] * 6, [256] * 6, 4, 1, 2, "units", 1),     # many waves of long full tiles
+    ([66000], [40], 4, 1, 256, "tiles", 230),         # past the staged block-table row if unsplit
+    ([66002] * 3, [2] * 3, 4, 1, 1, "halves", 1),     # past it in one 128-row workgroup
+    ([140000], [8], 4, 1, 1, "tiles", 2),             # past it in each key range
 ]
 
 
-@pytest.mark.parametrize("lens,new,hq,hkv,cus", CASES)
+@pytest.mark.parametrize("lens,new,hq,hkv,cus,form,parts", CASES)
 @pytest.mark.parametrize("small_ws", [False, True])
-def test_fine_tiles(lens, new, hq, hkv, cus, small_ws):
-    H.say(f"[case] fine tiles lens={lens} new={new} heads={hq}/{hkv} cus={cus} small={small_ws}")
+def test_fine_tiles(lens, new, hq, hkv, cus, form, parts, small_ws):
+    H.say(f"[case] fine tiles lens={lens} new={new} heads={hq}/{hkv} cus={cus} {form} small={small_ws}")
     b = wl.custom_batch(lens, q_lens=new, num_q_heads=hq, num_kv_heads=hkv, seed=7, append=True)
     cache = H.DeviceCache(b)
     plan = H.plan_for(b, num_cus=cus)

@@ -297,7 +297,9 @@ def test_two_plans_take_turns_on_one_workspace():
 
 
 def test_append_prior_longer_than_staged_block_table():
-    """A chunk whose keys span more pages than the chunk kernel stages in LDS (4096)."""
+    """A chunk whose keys span more pages than the chunk kernel stages in LDS (4096); with the
+    default plan they are split into ranges that fit (test_gpu_fine_tiles.py runs workgroups
+    that read past the staged ids)."""
     prior, chunk = 66000, 100
     H.say(f"[case] append long prior {prior} chunk {chunk}")
     b = wl.custom_batch([prior + chunk, 40], q_lens=[chunk, 1], num_q_heads=4, num_kv_heads=1,
@@ -422,10 +424,10 @@ def test_one_plan_shared_by_two_threads_and_streams():
 
 @pytest.mark.parametrize("group,hkv", [(1, 4), (3, 2), (5, 8), (7, 4), (16, 1)])
 def test_merge_thread_groups_many_splits(group, hkv):
-    """Rows cut into many splits (up to 64) for each shape of the merge kernel's thread
-    groups: 16 groups of 16 threads at G = 1, 5 groups at G = 3, 3 groups (16 threads idle)
-    at G = 5, 2 at G = 7, one at G = 16; a row whose split count is not a multiple of the
-    group count and one with fewer splits than groups."""
+    """Rows cut into many splits (up to 64), into few and into none, at group sizes from one
+    head to 16: the merge kernel takes a block per head, whose 16 groups of 16 threads share
+    the splits; a row whose split count is not a multiple of the group count and one with
+    fewer splits than groups."""
     lens = [16 * 64 * 5 + 7, 16 * 40 + 3, 16 * 3, 1000]
     H.say(f"[case] merge groups G={group} hkv={hkv} lens={lens}")
     b = wl.custom_batch(lens, num_q_heads=group * hkv, num_kv_heads=hkv, seed=60 + group)

@@ -45,20 +45,25 @@ def _scale_keys(batch, rising: bool):
         batch.k_new = wl.f32_to_bf16_bits(k_new)
 
 
+PRIOR = [0, 3000, 700, 40, 1200]
+CHUNK = [700, 300, 1, 64, 1]
+
+
+@pytest.mark.parametrize("params", [dict(num_cus=8, units_per_cu=1, min_split_pages=2),
+                                    dict(num_cus=256)])
 @pytest.mark.parametrize("rising", [True, False])
-def test_append_with_moving_maximum(rising):
-    prior = [0, 3000, 700, 40, 1200]
-    chunk = [700, 300, 1, 64, 1]
-    lens = [p + c for p, c in zip(prior, chunk)]
-    H.say(f"[case] append, keys scaled {'up' if rising else 'down'} along the row")
-    b = wl.custom_batch(lens, q_lens=chunk, num_q_heads=16, num_kv_heads=4, seed=77)
+def test_append_with_moving_maximum(rising, params):
+    """Whole units on few CUs, and tiles whose keys are split over many."""
+    lens = [p + c for p, c in zip(PRIOR, CHUNK)]
+    H.say(f"[case] append, keys scaled {'up' if rising else 'down'} along the row {params}")
+    b = wl.custom_batch(lens, q_lens=CHUNK, num_q_heads=16, num_kv_heads=4, seed=77)
     _scale_keys(b, rising)
-    o, lse, cache, _ = H.run(b, plan_params=dict(num_cus=8, units_per_cu=1, min_split_pages=2))
+    o, lse, cache, _ = H.run(b, plan_params=params)
     ro, rl, _, _ = oracle.append_ref(b.q, b.k_new, b.v_new, b.k_pages, b.v_pages,
                                      b.block_table, b.seq_lens, b.q_lens, b.scale)
     spread = float(rl.max() - rl.min())
     H.say(f"  oracle LSE spread over rows {spread:.1f}")
-    H.assert_parity(o, lse, ro, rl, label=f"append moving max rising={rising}")
+    H.assert_parity(o, lse, ro, rl, label=f"append moving max rising={rising} {params}")
     cache.close()
 
 

@@ -90,3 +90,21 @@ def test_chunk_tiles_are_not_cut_where_decode_rows_fill_the_chip(driver):
              (4, 64, 4000, 127, 1000, False), (4, 64, 16000, 16, 16000, True)]
     got = forms(driver, [form(*c[:5]) for c in cases])
     assert [f["parts"] > 1 for f in got] == [c[5] for c in cases]
+
+
+def test_gpu_cases_take_the_forms_they_are_for(driver):
+    """The GPU tests of the launched forms run what they say."""
+    import test_gpu_fewer_units as fewer
+    import test_gpu_fine_tiles as fine
+    import test_gpu_softmax_range as moving
+
+    got = forms(driver, [line(c[0], c[1], *c[2:5]) for c in fine.CASES])
+    assert [(f["form"], f["parts"]) for f in got] == [c[5:] for c in fine.CASES]
+    longest = [f["pages"] for c, f in zip(fine.CASES, got) if c[0][0] >= 66000]
+    assert longest[0] < 4096 < min(longest[1:])        # pages of a workgroup against the staged row
+    got = forms(driver, [line(c[0], None, *c[1:4]) for c in fewer.CASES])
+    assert [f["singles"] for f in got] == [c[4] for c in fewer.CASES]
+    assert [f["singles"] < f["table_singles"] for f in got] == [True] * 7 + [False] * 2
+    lens = [p + c for p, c in zip(moving.PRIOR, moving.CHUNK)]
+    got = forms(driver, [line(lens, moving.CHUNK, 16, 4, c) for c in (8, 256)])
+    assert got[0]["form"] == "units" and got[1]["form"] == "tiles" and got[1]["parts"] > 1
