@@ -45,7 +45,6 @@
 // Skipping the ring's copies past the last key, starting the first copies from scalar page
 // ids and storing whole rows through LDS took 32 prompts of 64-2,048 tokens (40/8 heads)
 // from 860 us to 820 us.
-#include <algorithm>
 #include <cfloat>
 #include <cmath>
 #include <type_traits>
@@ -84,6 +83,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 struct ChunkArgs {
   const uint16_t* k_cache;
   const uint16_t* v_cache;
+  const int32_t* units;
   const int32_t* tiles;
   const int32_t* bt;
   const uint16_t* q;
@@ -96,7 +96,7 @@ struct ChunkArgs {
   int hq;
   int group;
   float sl2;
-  int halves;       // narrow form: halves per unit, or 0 where `tiles` holds fine tiles
+  int form;         // ChunkForm
   int half_tokens;  // tokens that a unit's first half touches
   int32_t xcd_first[kNumXcds];  // each XCD queue's first record and workgroup count
   int32_t xcd_count[kNumXcds];
@@ -148,8 +148,7 @@ void chunk_kernel(ChunkArgs A) {
   const int xcd = blockIdx.x % kNumXcds;
   const int slot = blockIdx.x / kNumXcds;
   if (slot >= A.xcd_count[xcd]) return;
-  const int shift = !kWide && A.halves == 2 ? 1 : 0;
-  const size_t rec = size_t(A.xcd_first[xcd] + (slot >> shift));
+  const size_t rec = size_t(A.xcd_first[xcd] + slot);
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int col = lane & 31, hh = lane >> 5;  // accumulator column (tile row), lane half
@@ -160,18 +159,18 @@ void chunk_kernel(ChunkArgs A) {
   // half of a unit's rows: over the keys that they see, straight from the unit's record, or
   // over one split of them, from a fine tile's.
   int b, g, q0, q1, row0, prior, kv0, kv1, r_first, nsplit, part;
-  if (kWide || A.halves) {
-    const int32_t* u = A.tiles + rec * kUnitInts;
-    b = u[U_B], g = u[U_G], q0 = u[U_Q0], q1 = u[U_Q1], row0 = u[U_ROW0], prior = u[U_PRIOR];
-    kv0 = 0, kv1 = u[U_KV1], r_first = 0, nsplit = 1, part = 0;
-    if (!kWide) {
-      if (slot & shift) {
-        r_first = kRows;
-        if (kRows >= (q1 - q0) * G) return;  // no second half
-      } else {
-        kv1 = min(kv1, prior + q0 + A.half_tokens);
-      }
+  if (kWide || A.form != kFineTiles) {
+    size_t unit = rec;
+    int half = 0;
+    if (!kWide && A.form == kBothHalves) {
+      unit = size_t(A.xcd_first[xcd] + (slot >> 1)), half = slot & 1;
+    } else if (!kWide && A.form == kListedHalves) {
+      unit = size_t(A.tiles[rec] >> 1), half = A.tiles[rec] & 1;
     }
+    const int32_t* u = A.units + unit * kUnitInts;
+    b = u[U_B], g = u[U_G], q0 = u[U_Q0], q1 = u[U_Q1], row0 = u[U_ROW0], prior = u[U_PRIOR];
+    kv0 = 0, kv1 = u[U_KV1], r_first = half * kRows, nsplit = 1, part = 0;
+    if (!kWide && !half) kv1 = min(kv1, prior + q0 + A.half_tokens);
   } else {
     const int32_t* u = A.tiles + rec * kTileInts;
     b = u[T_B], g = u[T_GH] & 0xFFFF, q0 = u[T_Q0], q1 = u[T_Q1], row0 = u[T_ROW0];
@@ -561,14 +560,13 @@ hipError_t launch_chunk(const KvLayout& L, const Plan& P, void* ws, const void* 
   ChunkArgs A;
   A.k_cache = static_cast<const uint16_t*>(L.desc.k_cache);
   A.v_cache = static_cast<const uint16_t*>(L.desc.v_cache);
-  A.tiles = reinterpret_cast<const int32_t*>(
-      w + (P.fine_tiles ? P.off_tiles
-                        : P.off_units + size_t(P.info.n_single) * kUnitInts * sizeof(int32_t)));
-  A.halves = P.halves;
+  A.units = reinterpret_cast<const int32_t*>(w + P.off_units) + size_t(P.info.n_single) * kUnitInts;
+  A.tiles = reinterpret_cast<const int32_t*>(w + P.off_tiles);
+  A.form = P.chunk_form;
   A.half_tokens = (kTileRows - 1) / P.group + 1;
   for (int x = 0; x < kNumXcds; ++x) {
     A.xcd_first[x] = P.xcd_map[size_t(2 * x)];
-    A.xcd_count[x] = P.xcd_map[size_t(2 * x + 1)] * std::max(1, P.halves);
+    A.xcd_count[x] = P.xcd_map[size_t(2 * x + 1)] * (P.chunk_form == kBothHalves ? 2 : 1);
   }
   A.bt = bt;
   A.q = static_cast<const uint16_t*>(q);
@@ -581,7 +579,7 @@ hipError_t launch_chunk(const KvLayout& L, const Plan& P, void* ws, const void* 
   A.hq = P.num_q_heads;
   A.group = P.group;
   A.sl2 = scale * kLog2e;
-  if (P.fine_tiles || P.halves)
+  if (P.chunk_form != kUnits)
     hipLaunchKernelGGL(chunk_kernel<kNarrowWaves>, dim3(unsigned(P.chunk_grid)),
                        dim3(64 * kNarrowWaves), 0, s, A);
   else

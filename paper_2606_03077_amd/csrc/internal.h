@@ -22,17 +22,14 @@ struct Plan {
   std::vector<int32_t> units;   // n_units * kUnitInts
   std::vector<int32_t> writes;  // n_write_tiles * kWriteInts (append only)
   std::vector<int32_t> merges;  // n_merge_groups * kMergeInts
-  std::vector<int32_t> xcd_map; // (first chunk unit or fine tile, count) per XCD queue
+  std::vector<int32_t> xcd_map; // (first chunk unit or entry of tiles, count) per XCD queue
   int64_t chunk_grid = 0;       // workgroups of the chunk launch: kNumXcds * longest queue
-  // What a chunk workgroup takes: a chunk unit, half h of one (halves: 1 if no unit has more
-  // than kTileRows rows, else 2), or a fine tile of the table.
-  int32_t halves = 0;
-  bool fine_tiles = false;
-  std::vector<int32_t> tiles;   // fine tiles, kTileInts each
+  ChunkForm chunk_form = kUnits;
+  std::vector<int32_t> tiles;   // listed halves, or fine tiles of kTileInts each
   std::vector<int32_t> chunk_merges;  // kMergeInts per fine tile whose keys are split
 
   // Workspace: [units | writes | merges | partial o | partial lse], and behind it, where the
-  // launch takes a table of fine tiles, [fine tiles | chunk merges | chunk partial o |
+  // launch takes fine tiles from a table, [fine tiles | chunk merges | chunk partial o |
   // chunk partial lse]; all 256-B aligned.
   size_t off_units = 0, off_tiles = 0, off_writes = 0, off_merges = 0, off_chunk_merges = 0,
          off_part_o = 0, off_part_lse = 0, off_chunk_o = 0, off_chunk_lse = 0;

@@ -157,9 +157,10 @@ std::unique_ptr<Plan> sibling(const Plan& P) {
 // Chooses the form of the chunk launch: chunk units on workgroups of kChunkRows rows (eight
 // waves, one per CU), or fine tiles of kTileRows rows (four waves, two workgroups per CU)
 // where that is faster.  Whole fine tiles in many waves are the halves of the units, in their
-// queues' order, and need no table of their own (P.halves); those of a single wave, whose keys
-// may be split, get one (P.fine).  Built without a table of many thousand tiles, a plan costs
-// the host what one of units does (32 prompts of 64-2,048 tokens 149 us, with it 310 us).
+// queues' order, read from the unit table, with a list of them where some units have only one;
+// those of a single wave, whose keys may be split, get records of their own.  Built without a
+// record for each of many thousand tiles, a plan costs the host about what one of units does
+// (80 prompts of 510 tokens 154 us as units, 158 as halves, 314 with records).
 // single_pages: pages of the decode rows beside them, over the KV heads; longest_queue: units
 // of the longest queue.
 //
@@ -216,16 +217,13 @@ void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t single_pag
                 int64_t longest_queue, Plan& P) {
   const int64_t cus = P.params.num_cus, Hkv = P.num_kv_heads, G = P.group;
   const int64_t S = std::min<int64_t>(2 * cus, kMaxFineSlots);
-  int64_t n = 0, units = 0, longest = 0, total = 0, longest_unit = 0, wide_cost = 0, halves = 1;
+  int64_t n = 0, units = 0, longest = 0, total = 0, longest_unit = 0, wide_cost = 0;
   for (const ChunkRow& r : rows) {
     each_tile(r, T, G, [&](const Tile& t) {
       n += Hkv;
       longest = std::max(longest, t.steps);
       total += Hkv * t.steps;
-      if (t.h) {
-        halves = 2;
-        return;
-      }
+      if (t.h) return;
       const int64_t unit_steps = ceil_div(r.prior + t.q1, kChunkStepKeys);
       units += Hkv;
       longest_unit = std::max(longest_unit, unit_steps);
@@ -235,10 +233,34 @@ void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t single_pag
   if (n == 0) return;
   const int64_t bias = single_pages ? 95 : 100;  // of the units' time, beside decode rows
   if (n > S) {
-    if (wide_cost * bias > 100 * (46 * total + 330 * n)) {  // the units' queues and tables serve as they are
-      P.halves = int32_t(halves);
-      P.chunk_grid = kNumXcds * longest_queue * halves;
+    if (wide_cost * bias <= 100 * (46 * total + 330 * n)) return;
+    if (n == units || n == 2 * units) {  // the units' queues and tables serve as they are
+      P.chunk_form = n == units ? kFirstHalves : kBothHalves;
+      P.chunk_grid = kNumXcds * longest_queue * (n / units);
+      return;
     }
+    // A list of the halves that there are: workgroups without one would take their turn in the
+    // dispatch over the shader engines, and where every fourth has none a quarter of the CUs
+    // waits (73 tokens of 40/8 heads on 3,600 for 32 requests 477 us without a list, 428 with).
+    auto Q = sibling(P);
+    Q->chunk_form = kListedHalves;
+    Q->tiles.reserve(size_t(n));
+    const int32_t* u = P.units.data() + size_t(P.info.n_single) * kUnitInts;
+    int64_t longest_run = 0;
+    for (size_t x = 0; x < kNumXcds; ++x) {
+      const int32_t first = int32_t(Q->tiles.size());
+      const int32_t end = P.xcd_map[2 * x] + P.xcd_map[2 * x + 1];
+      for (int32_t i = P.xcd_map[2 * x]; i < end; ++i, u += kUnitInts) {
+        Q->tiles.push_back(i << 1);
+        if ((u[U_Q1] - u[U_Q0]) * G > kTileRows) Q->tiles.push_back(i << 1 | 1);
+      }
+      Q->xcd_map.push_back(first);
+      Q->xcd_map.push_back(int32_t(Q->tiles.size()) - first);
+      longest_run = std::max<int64_t>(longest_run, Q->xcd_map.back());
+    }
+    Q->chunk_grid = kNumXcds * longest_run;
+    fine_layout(*Q, P, 0);
+    P.fine = std::move(Q);
     return;
   }
 
@@ -279,7 +301,7 @@ void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t single_pag
   // list cut into eight runs of equal cost, one per XCD, so that they share an L2; each
   // queue its longest piece first.
   auto Q = sibling(P);
-  Q->fine_tiles = true;
+  Q->chunk_form = kFineTiles;
   struct Piece { int32_t rec[kTileInts]; int64_t steps; };
   std::vector<std::vector<Piece>> queues(kNumXcds);
   for (auto& q : queues) q.reserve(size_t(S / kNumXcds + 1));
@@ -632,7 +654,6 @@ libra_status build_plan(const libra_plan_desc& d, const int32_t* seq_lens, const
 
   P.xcd_map.assign(xcd_map, xcd_map + 2 * kNumXcds);
   P.chunk_grid = int64_t(kNumXcds) * longest;
-  P.halves = 0;
 
   // Split-merge table: every single row with n_b > 1, per KV head, ascending (b, g).
   auto merge_table = [&](const std::vector<int64_t>& n, const std::vector<int64_t>& base) {

@@ -26,10 +26,15 @@ constexpr int kChunkRows = 256;  // most (token, head) rows of one query tile
 constexpr int kTileRows = 128;   // rows of a fine tile: a query tile is one or two of them
 constexpr int kTileStepKeys = 32;  // keys per step of the chunk kernel on fine tiles
 
-// Fine tiles: one record per workgroup of the chunk kernel's narrow form where they fit in one
-// wave (whole tiles in many waves are taken from the unit table).  A workgroup takes rows
-// [128 h, 128 h + 128) of the query tile [q0, q1) of (sequence b, KV head g), T_GH =
-// g | h << 16, over keys [kv0, kv1): all of them, or split `part` of n.
+// What a workgroup of the chunk launch takes: a query tile (wide form, kChunkRows rows), or a
+// fine tile (narrow form, kTileRows rows), which is half h of a query tile over the keys that
+// it sees (of tiles of one half each; of both halves of every tile; or as a table lists them,
+// query tile << 1 | h), or, where they fit in one wave, over all keys or a split, as a record
+// of the fine-tile table has it.
+enum ChunkForm : int { kUnits = 0, kFirstHalves, kBothHalves, kListedHalves, kFineTiles };
+
+// Fine tiles: rows [128 h, 128 h + 128) of the query tile [q0, q1) of (sequence b, KV head g),
+// T_GH = g | h << 16, over keys [kv0, kv1): all of them, or split `part` of n.
 enum TileField : int { T_B = 0, T_GH, T_Q0, T_Q1, T_ROW0, T_PRIOR, T_KV0, T_KV1, T_PART, T_NSPLIT };
 constexpr int kTileInts = 10;
 

@@ -7,7 +7,7 @@ struct FakeHipCounters {
   long memcpy_async = 0;
   long stream_create = 0, stream_wait = 0;
   long launches = 0;
-  long fine_launches = 0;  // chunk launches that take fine tiles
+  long fine_launches = 0;  // chunk launches that take fine tiles from a table
   long stale_tables = 0;   // decode / chunk launches whose tables are not in the workspace
 
   long allocations() const { return host_malloc + host_free + device_malloc + device_free +

@@ -49,28 +49,33 @@ std::vector<Group> chunk_groups(const Plan& P, const Plan& base) {
   for (int x = 0; x < kNumXcds; ++x) {
     const int f = P.xcd_map[size_t(2 * x)], c = P.xcd_map[size_t(2 * x + 1)];
     CHECK(x == 0 ? f == 0 : f == P.xcd_map[size_t(2 * x - 2)] + P.xcd_map[size_t(2 * x - 1)]);
-    longest = std::max<int64_t>(longest, int64_t(c) * std::max(1, P.halves));
-    for (int i = f; i < f + c; ++i) {
-      if (P.fine_tiles) {
-        CHECK(size_t(i + 1) * kTileInts <= P.tiles.size());
-        const int32_t* t = P.tiles.data() + size_t(i) * kTileInts;
+    const int per = P.chunk_form == kBothHalves ? 2 : 1;
+    longest = std::max<int64_t>(longest, int64_t(c) * per);
+    for (int slot = 0; slot < c * per; ++slot) {
+      if (P.chunk_form == kFineTiles) {
+        CHECK(size_t(f + slot + 1) * kTileInts <= P.tiles.size());
+        const int32_t* t = P.tiles.data() + size_t(f + slot) * kTileInts;
         out.push_back({t[T_B], t[T_GH] & 0xFFFF, t[T_Q0], t[T_Q1], (t[T_GH] >> 16) * kTileRows,
                        kTileRows, t[T_ROW0], t[T_PRIOR], t[T_KV0], t[T_KV1], t[T_PART],
                        t[T_NSPLIT]});
         continue;
       }
-      CHECK((first + size_t(i) + 1) * kUnitInts <= units.size());
-      const int32_t* u = units.data() + (first + size_t(i)) * kUnitInts;
-      CHECK(u[U_KIND] == kKindChunk);
-      for (int h = 0; h < std::max(1, P.halves); ++h) {
-        const int rows = P.halves ? kTileRows : kChunkRows;
-        if (h * rows >= (u[U_Q1] - u[U_Q0]) * P.group) continue;  // no second half
-        const int kv1 = P.halves && h == 0
-                            ? std::min(u[U_KV1], u[U_PRIOR] + u[U_Q0] + (kTileRows - 1) / P.group + 1)
-                            : u[U_KV1];
-        out.push_back({u[U_B], u[U_G], u[U_Q0], u[U_Q1], h * rows, rows, u[U_ROW0], u[U_PRIOR], 0,
-                       kv1, -1, 1});
+      int unit = f + slot / per, h = slot % per;
+      if (P.chunk_form == kListedHalves) {
+        CHECK(size_t(f + slot) < P.tiles.size());
+        unit = P.tiles[size_t(f + slot)] >> 1, h = P.tiles[size_t(f + slot)] & 1;
       }
+      CHECK((first + size_t(unit) + 1) * kUnitInts <= units.size());
+      const int32_t* u = units.data() + (first + size_t(unit)) * kUnitInts;
+      CHECK(u[U_KIND] == kKindChunk);
+      const bool narrow = P.chunk_form != kUnits;
+      const int rows = narrow ? kTileRows : kChunkRows;
+      CHECK(h * rows < (u[U_Q1] - u[U_Q0]) * P.group);  // no workgroup without rows
+      const int kv1 = narrow && h == 0
+                          ? std::min(u[U_KV1], u[U_PRIOR] + u[U_Q0] + (kTileRows - 1) / P.group + 1)
+                          : u[U_KV1];
+      out.push_back({u[U_B], u[U_G], u[U_Q0], u[U_Q1], h * rows, rows, u[U_ROW0], u[U_PRIOR], 0, kv1,
+                     -1, 1});
     }
   }
   CHECK(P.chunk_grid == kNumXcds * longest);
@@ -206,7 +211,8 @@ int main() {
     if (P.base) CHECK(P.upload_off >= plan.ws_bytes && P.off_tiles >= plan.ws_bytes);
     CHECK(parts.empty() || *parts.rbegin() + 1 == int(parts.size()));
 
-    const char* form = groups.empty() ? "none" : P.fine_tiles ? "tiles" : P.halves ? "halves" : "units";
+    const char* const names[] = {"units", "halves", "halves", "listed", "tiles"};
+    const char* form = groups.empty() ? "none" : names[P.chunk_form];
     std::printf("%s %zu %d %d %d %d %d %zu %zu\n", form, groups.size(), most_parts, widest,
                 P.info.n_single, plan.info.n_single, most_splits, P.ws_bytes, plan.ws_bytes);
   }

@@ -20,7 +20,8 @@ static void check_units(const libra::Plan& P, const void* ws, bool chunk) {
   check_table(ws, P.off_units, units, chunk ? n : 0, chunk ? units.size() : n);
 }
 static void check_chunk(const libra::Plan& P, const void* ws) {
-  if (!P.fine_tiles) return check_units(P, ws, true);
+  if (P.chunk_form != libra::kFineTiles) check_units(P, ws, true);
+  if (P.tiles.empty()) return;
   ++g_fake_hip.fine_launches;
   check_table(ws, P.off_tiles, P.tiles, 0, P.tiles.size());
   check_table(ws, P.off_chunk_merges, P.chunk_merges, 0, P.chunk_merges.size());

@@ -1,8 +1,8 @@
 """Append tiles cut by rows and keys: the forms of the chunk launch against the oracle.
 
 Few chunk tiles run as 128-row workgroups whose keys may be split, with the partials merged
-("tiles"); short or half-filled ones in many waves as halves of their units ("halves"); many
-long full ones, or those beside decode rows that fill the chip, as whole 256-row tiles
+("tiles"); short or half-filled ones in many waves as halves of their units ("halves", or
+"listed" where only some units have two); many long full ones, or those beside decode rows that fill the chip, as whole 256-row tiles
 ("units").  The cases sit at the edges: rows of one head group at and beside 128 and 256, key
 counts at and beside the 32-key step and the smallest piece, rows that see no key of a split,
 one-token tails, more pages than the staged block-table row holds, and the workspace that is
@@ -32,9 +32,10 @@ CASES = [
     ([900], [850], 8, 8, 256, "tiles", 4),            # rows that see no key of the later splits
     ([6000], [10], 16, 1, 8, "tiles", 8),             # 16-head groups, few slots
     ([6000], [90], 16, 1, 8, "units", 1),             # and enough tiles of them for whole units
-    ([130] * 12, [130] * 12, 8, 1, 2, "halves", 1),   # more full tiles than slots
+    ([128] * 12, [128] * 12, 8, 1, 2, "halves", 1),   # more full tiles than slots
+    ([130] * 12, [130] * 12, 8, 1, 2, "listed", 1),   # and a few half-filled ones among them
     ([400] * 9, [20] * 9, 8, 2, 4, "halves", 1),      # many waves of half-filled tiles
-    ([700] * 5, [37] * 5, 14, 2, 4, "halves", 1),     # and of second halves of few rows
+    ([700] * 5, [37] * 5, 14, 2, 4, "listed", 1),     # and of second halves of few rows
     ([3000] * 6, [256] * 6, 4, 1, 2, "units", 1),     # many waves of long full tiles
     ([66000], [40], 4, 1, 256, "tiles", 230),         # past the staged block-table row if unsplit
     ([66002] * 3, [2] * 3, 4, 1, 1, "halves", 1),     # past it in one 128-row workgroup

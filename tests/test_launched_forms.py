@@ -64,15 +64,15 @@ def test_random_launches_cover_every_key_once(driver):
                           rng.choice([3, 3, 1, 2]), rng.choice([16, 1, 2]), rng.choice([64, 128, 3]),
                           q_tile))
     got = forms(driver, lines)
-    assert {f["form"] for f in got} == {"none", "units", "halves", "tiles"}
+    assert {f["form"] for f in got} == {"none", "units", "halves", "listed", "tiles"}
     assert any(f["singles"] < f["table_singles"] for f in got)
 
 
 def test_whole_tiles_in_many_waves_have_no_table(driver):
     """Short prompts run as halves of their units: nothing is built or uploaded for them
     beyond the plan's own tables."""
-    prompts = [64 + 61 * i for i in range(32)]
-    short, long = forms(driver, [line(prompts, prompts, 40, 8), line([40960], [40960], 40, 8)])
+    short, long = forms(driver, [line([510] * 80, [510] * 80, 40, 8),
+                                 line([40960], [40960], 40, 8)])
     assert short["form"] == "halves" and short["workspace"] == short["plain"]
     assert long["form"] == "units" and long["workspace"] == long["plain"]
 
