@@ -170,27 +170,33 @@ std::unique_ptr<Plan> sibling(const Plan& P) {
 // write float32 partials, which a merge combines.  The forms are compared by the times
 // below, in 10 ns, measured over appends of 8 to 1,600 tokens to 1 to 128 requests (256 CUs):
 // * a 64-key step of a wide workgroup takes 1.25 us while half of the CUs are idle, 1.67 us
-//   when all are busy, and a workgroup 8-9 us besides (dispatch, first loads, stores);
-// * a 32-key step of a fine tile takes 0.65 us alone on a CU and 0.91-0.93 us beside
-//   another, a tile 3.3 us of its CU besides (7 us by itself), a split launch and its merge
+//   when all are busy, and a workgroup 8-9 us besides (dispatch, first loads, stores); less
+//   than a wave of units is as busy as their mean is to the longest (236 units of unequal
+//   lengths, at most 20,500 keys, 457 us, cut tiles 528 us);
+// * a 32-key step of a fine tile takes 0.65 us alone on a CU and 0.93-0.96 us beside
+//   another, a tile 3.5 us of its CU besides (7 us by itself), a split launch and its merge
 //   13 us more (496 tokens on 431, at most 29 steps: 25 us whole, 35 us split in four).
-// So full tiles in many waves stay wide from about 15 steps on (20 prompts of 2,040 tokens
+// So full tiles in many waves stay wide from about 12 steps on (20 prompts of 2,040 tokens
 // 974 us against 984 us, 10 of 4,080 1,642 and 1,716 us, 40,960-token prefill 13.8 and
 // 15.0 ms), and fine tiles take shorter ones (80 prompts of 510 tokens 470 us against 515 us,
-// 64 x 100 tokens on 500 78 and 81 us), query tiles of at most 128 rows (128 x 20 tokens on
-// 2,000, 4 heads per KV head: 218 and 266 us) and launches that leave CUs idle (333 tokens on
+// 16 of 230-911 99 and 109 us) and query tiles of at most 128 rows (128 x 20 tokens on 2,000,
+// 4 heads per KV head: 218 and 266 us); over 140 appends of 8-1,024 tokens to 4-128 requests
+// whose modelled times differ by less than 12%, the form chosen takes 0.3% more than the
+// better one on average, at most 4%.  Launches that leave CUs idle are cut (333 tokens on
 // 16,001: 129 and 326 us; 800 on 16,000: 267 and 340 us; 4 x 8 on 30,000: 54 and 583 us).
 // Decode rows run beside the chunk launch, which is dispatched first: they take about 330 ns
-// per page of a CU, start some 12 us later (the fork) and find the share of the CUs that the
-// chunk workgroups leave, so a form ends after max(t, 12 us + decode + t * share it fills); a
-// fine tile shares its CU with them (0.93 us a step), a wide workgroup's LDS keeps them off.
-// Tiles cut to fill the chip then only pay where whole units would outlast the decode rows,
-// and units are taken up to 5% above, as their CUs serve the decode rows' last wave better.
+// per page of a CU, start up to 12 us later (the fork) and find the share of the CUs that the
+// chunk workgroups leave, so a form ends after max(t, lag + decode + t * share it fills).  A
+// fine tile shares its CU with them (steps of 0.65 us become 0.93 us meanwhile), a wide
+// workgroup's LDS keeps them off.  Tiles cut to fill the chip then only pay where whole units
+// would outlast the decode rows, and where units would not, they are taken up to 5% above, as
+// their CUs serve the decode rows' last wave better.
 // Measured with 32 heads on 8 KV heads, cut tiles and units: 333 tokens on 4,000 alone 45 and
 // 94 us, beside 16 rows of 1,000 78 and 107 us, beside 127 of them 149 and 121 us; on 16,000
 // beside 127 of 1,000 206 and 335 us, of 4,000 441 and 379 us (whole tiles 411 us); 20 tokens
-// on 430 beside 16 rows of 16,000 206 us as whole tiles, 189 us as units; 8 x 300 on 500 (more
-// than a wave) beside 16 rows of 16,000 243 and 235 us.
+// on 430 beside 16 rows of 16,000 206 us as whole tiles, 189 us as units.  Over 287 random
+// batches of 1-64 chunk rows beside 1-128 decode rows, launched from a graph, the form chosen
+// takes 0.9% more than the best of the three on average (1.8% if they are left out of view).
 constexpr int64_t kMinPieceSteps = 8;
 constexpr int64_t kMaxFineSlots = 2048;  // bounds the partial results (64.5 KiB each)
 
@@ -217,7 +223,7 @@ void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t single_pag
                 int64_t longest_queue, Plan& P) {
   const int64_t cus = P.params.num_cus, Hkv = P.num_kv_heads, G = P.group;
   const int64_t S = std::min<int64_t>(2 * cus, kMaxFineSlots);
-  int64_t n = 0, units = 0, longest = 0, total = 0, longest_unit = 0, wide_cost = 0;
+  int64_t n = 0, units = 0, longest = 0, total = 0, longest_unit = 0, unit_total = 0;
   for (const ChunkRow& r : rows) {
     each_tile(r, T, G, [&](const Tile& t) {
       n += Hkv;
@@ -227,13 +233,12 @@ void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t single_pag
       const int64_t unit_steps = ceil_div(r.prior + t.q1, kChunkStepKeys);
       units += Hkv;
       longest_unit = std::max(longest_unit, unit_steps);
-      wide_cost += Hkv * (167 * unit_steps + 840);
+      unit_total += Hkv * unit_steps;
     });
   }
   if (n == 0) return;
-  const int64_t bias = single_pages ? 95 : 100;  // of the units' time, beside decode rows
   if (n > S) {
-    if (wide_cost * bias <= 100 * (46 * total + 330 * n)) return;
+    if (167 * unit_total + 840 * units <= 48 * total + 350 * n) return;
     if (n == units || n == 2 * units) {  // the units' queues and tables serve as they are
       P.chunk_form = n == units ? kFirstHalves : kBothHalves;
       P.chunk_grid = kNumXcds * longest_queue * (n / units);
@@ -241,7 +246,8 @@ void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t single_pag
     }
     // A list of the halves that there are: workgroups without one would take their turn in the
     // dispatch over the shader engines, and where every fourth has none a quarter of the CUs
-    // waits (73 tokens of 40/8 heads on 3,600 for 32 requests 477 us without a list, 428 with).
+    // waits (25-73 tokens of 40/8 heads on 5,500-14,500 for 32 requests: 477 us with such
+    // workgroups, 437 us with a list and 436 us from full records).
     auto Q = sibling(P);
     Q->chunk_form = kListedHalves;
     Q->tiles.reserve(size_t(n));
@@ -284,18 +290,23 @@ void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t single_pag
     else t = mid + 1;
   }
   const int64_t single_time = 33 * single_pages / cus;
+  const int64_t lag = std::min<int64_t>(1200, 8 * single_time);
   auto beside = [&](int64_t time, int64_t groups, int64_t room) {
-    if (single_pages == 0) return time;
-    return std::max(time, 1200 + single_time + time * std::min(groups, room) / room);
+    return std::max(time, lag + single_time + time * std::min(groups, room) / room);
   };
-  auto step = [&](int64_t groups) { return groups <= cus && single_pages == 0 ? 65 : 93; };
-  const int64_t cut = pieces(t);
-  const int64_t whole_time = beside(longest * step(n) + 700, n, 2 * cus);
-  const int64_t split_time = beside(t * step(cut) + 2000, cut, 2 * cus);
+  auto fine_time = [&](int64_t steps, int64_t groups, int64_t fixed) {
+    const int64_t time = steps * (groups <= cus ? 65 : 93) + fixed;
+    const int64_t shared = groups <= cus ? 43 * std::min(time, single_time) / 100 : 0;
+    return beside(time + shared, groups, 2 * cus);
+  };
+  const int64_t whole_time = fine_time(longest, n, 700);
+  const int64_t split_time = fine_time(t, pieces(t), 2000);
   if (split_time < whole_time) piece = t;
-  const int64_t wide_step = std::max<int64_t>(125, 80 + 90 * units / cus);
-  const int64_t wide_time = beside(longest_unit * wide_step + 800, units, cus);
-  if (units <= cus && wide_time * bias < 100 * std::min(whole_time, split_time)) return;
+  const int64_t unit_step = std::max<int64_t>(125, 80 + 90 * unit_total / (longest_unit * cus));
+  const int64_t unit_time = longest_unit * unit_step + 800;
+  const int64_t bias = single_time > unit_time ? 95 : 100;
+  if (units <= cus && beside(unit_time, units, cus) * bias < 100 * std::min(whole_time, split_time))
+    return;
 
   // Pieces that read the same keys next to each other (by row, KV head and key range), the
   // list cut into eight runs of equal cost, one per XCD, so that they share an L2; each

@@ -70,9 +70,13 @@ def test_random_launches_cover_every_key_once(driver):
 
 def test_whole_tiles_in_many_waves_have_no_table(driver):
     """Short prompts run as halves of their units: nothing is built or uploaded for them
-    beyond the plan's own tables."""
-    short, long = forms(driver, [line([510] * 80, [510] * 80, 40, 8),
-                                 line([40960], [40960], 40, 8)])
+    beyond the plan's own tables.  Longer ones run as whole units, between them the form that
+    is faster: 20 tokens to each of 128 requests, but not prompts of 64-2,048 tokens."""
+    prompts = [64 + 61 * i for i in range(32)]
+    short, long, few, mixed = forms(driver, [
+        line([510] * 80, [510] * 80, 40, 8), line([40960], [40960], 40, 8),
+        line([2020] * 128, [20] * 128, 32, 8), line(prompts, prompts, 40, 8)])
+    assert few["form"] == "halves" and mixed["form"] == "units"
     assert short["form"] == "halves" and short["workspace"] == short["plain"]
     assert long["form"] == "units" and long["workspace"] == long["plain"]
 
