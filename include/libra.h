@@ -214,9 +214,9 @@ libra_status libra_kv_reshard_host(const void* const* src, int32_t n_src, int32_
  * 7. A chunk row is cut into query tiles of T tokens (T = q_tile, or floor(256 / G) if
  *    q_tile = 0): tile k holds new tokens [kT, min(kT + T, C_b)) and keys
  *    [0, P_b + min(kT + T, C_b)), P_b = L_b - C_b.  The unit table does not split them
- *    along KV; where whole tiles would leave compute units idle, the chunk launch cuts them
- *    by rows and keys into finer workgroups, whose partial results a merge combines (below,
- *    libra_plan_workspace_bytes).
+ *    along KV; the chunk launch may cut short or half-filled ones by rows, and where whole
+ *    tiles would leave compute units idle by keys too, whose partial results a merge
+ *    combines (below, libra_plan_workspace_bytes).
  * 8. Every unit is repeated for each KV head g.
  * 9. Single units come first, by descending KV tokens, ties by ascending (b, g, j).
  *    Chunk units follow, grouped per (b, g) and dealt to 8 per-XCD queues: a tile costs
@@ -329,9 +329,10 @@ libra_status libra_plan_get_units(libra_plan plan, const int32_t** units_host, i
 libra_status libra_plan_get_info(libra_plan plan, libra_plan_info* info);
 /* Bytes of device workspace the plan's calls need (unit, write and merge tables and the
  * float32 partial results of split rows).  An append plan whose chunk tiles are cut further
- * (step 7) counts the finer tables and partial results too, at most about 33 MB per 256
- * compute units (64.5 KiB for each of up to 2 num_cus partials, at most 2048); it also runs,
- * unsplit, in a workspace too small for those but large enough for the rest. */
+ * (step 7) may count a table of the parts and their partial results too, at most about 33 MB
+ * per 256 compute units (64.5 KiB for each of up to 2 num_cus partials, at most 2048); it
+ * also runs, with whole tiles, in a workspace too small for those but large enough for the
+ * rest. */
 size_t libra_plan_workspace_bytes(libra_plan plan);
 /* Copies the plan's tables into `workspace` (device) on `stream`.  Decode / append calls
  * do this themselves unless this plan was the last one to upload to that address;

@@ -3,8 +3,8 @@
 // Two forms of one kernel.  The wide form is a 512-thread workgroup (8 waves, two per SIMD,
 // one workgroup per CU) per chunk unit (sequence b, KV head g, new tokens [q0, q1)), up to
 // 256 query rows.  The narrow form is a 256-thread workgroup (4 waves, two workgroups per
-// CU) per fine tile: half of a unit's rows, over all of its keys or one split of them (the
-// plan decides; the rule and its measurements stand in plan.cpp).  Query rows are the
+// CU) per fine tile: half of a unit's rows, over the keys that they see or one split of them
+// (the plan decides; the rule and its measurements stand in plan.cpp).  Query rows are the
 // (token, head) pairs of the G heads sharing KV head g, token-major; wave w owns 32 of them
 // as the 32 columns of its matrix products.
 // Keys are visited 64 (wide) or 32 (narrow) at a time: a step of four pages, two page
@@ -43,8 +43,9 @@
 // (wide form 1.21-1.27 PFLOP/s on a 40,960-token prefill; the narrow form is 8% slower
 // there, as every 128 rows copy their own K and V), and the work per tile on short ones.
 // Skipping the ring's copies past the last key, starting the first copies from scalar page
-// ids and storing whole rows through LDS took 32 prompts of 64-2,048 tokens (40/8 heads)
-// from 860 us to 820 us.
+// ids and storing whole rows through LDS took 32 prompts of 64-2,048 tokens (40/8 heads) as
+// whole units from 893 us to 858 us on one card, cache write included; the narrow form takes
+// 857 us on them.
 #include <cfloat>
 #include <cmath>
 #include <type_traits>

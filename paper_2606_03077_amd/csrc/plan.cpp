@@ -170,9 +170,9 @@ std::unique_ptr<Plan> sibling(const Plan& P) {
 // write float32 partials, which a merge combines.  The forms are compared by the times
 // below, in 10 ns, measured over appends of 8 to 1,600 tokens to 1 to 128 requests (256 CUs):
 // * a 64-key step of a wide workgroup takes 1.25 us while half of the CUs are idle, 1.67 us
-//   when all are busy, and a workgroup 8-9 us besides (dispatch, first loads, stores); less
-//   than a wave of units is as busy as their mean is to the longest (236 units of unequal
-//   lengths, at most 20,500 keys, 457 us, cut tiles 528 us);
+//   when all are busy, and a workgroup 8-9 us besides (dispatch, first loads, stores); CUs
+//   whose unit is short are idle towards the end, so half of the units count by their length
+//   (236 of unequal lengths, at most 20,500 keys, 457 us, cut tiles 528 us);
 // * a 32-key step of a fine tile takes 0.65 us alone on a CU and 0.93-0.96 us beside
 //   another, a tile 3.5 us of its CU besides (7 us by itself), a split launch and its merge
 //   13 us more (496 tokens on 431, at most 29 steps: 25 us whole, 35 us split in four).
@@ -190,7 +190,10 @@ std::unique_ptr<Plan> sibling(const Plan& P) {
 // fine tile shares its CU with them (steps of 0.65 us become 0.93 us meanwhile), a wide
 // workgroup's LDS keeps them off.  Tiles cut to fill the chip then only pay where whole units
 // would outlast the decode rows, and where units would not, they are taken up to 5% above, as
-// their CUs serve the decode rows' last wave better.
+// their CUs serve the decode rows' last wave better.  Such a call also takes the host 45-50 us
+// (fork and join), and the launch that merges cut tiles 5 more, so what ends before is not cut
+// (4 x 26 tokens on 330 beside 12 rows 45.7 us, cut 51.3 us; from a graph 39 and 30 us; the
+// floor stands at 35 us, above which cutting gains more in a graph than it costs outside).
 // Measured with 32 heads on 8 KV heads, cut tiles and units: 333 tokens on 4,000 alone 45 and
 // 94 us, beside 16 rows of 1,000 78 and 107 us, beside 127 of them 149 and 121 us; on 16,000
 // beside 127 of 1,000 206 and 335 us, of 4,000 441 and 379 us (whole tiles 411 us); 20 tokens
@@ -291,21 +294,24 @@ void build_fine(const std::vector<ChunkRow>& rows, int64_t T, int64_t single_pag
   }
   const int64_t single_time = 33 * single_pages / cus;
   const int64_t lag = std::min<int64_t>(1200, 8 * single_time);
-  auto beside = [&](int64_t time, int64_t groups, int64_t room) {
-    return std::max(time, lag + single_time + time * std::min(groups, room) / room);
+  const int64_t host = single_pages ? 3500 : 0;
+  auto beside = [&](int64_t time, int64_t groups, int64_t room, int64_t least) {
+    return std::max({time, lag + single_time + time * std::min(groups, room) / room, least});
   };
-  auto fine_time = [&](int64_t steps, int64_t groups, int64_t fixed) {
+  auto fine_time = [&](int64_t steps, int64_t groups, int64_t fixed, int64_t least) {
     const int64_t time = steps * (groups <= cus ? 65 : 93) + fixed;
     const int64_t shared = groups <= cus ? 43 * std::min(time, single_time) / 100 : 0;
-    return beside(time + shared, groups, 2 * cus);
+    return beside(time + shared, groups, 2 * cus, least);
   };
-  const int64_t whole_time = fine_time(longest, n, 700);
-  const int64_t split_time = fine_time(t, pieces(t), 2000);
+  const int64_t whole_time = fine_time(longest, n, 700, host);
+  const int64_t split_time = fine_time(t, pieces(t), 2000, host ? host + 500 : 0);
   if (split_time < whole_time) piece = t;
-  const int64_t unit_step = std::max<int64_t>(125, 80 + 90 * unit_total / (longest_unit * cus));
+  const int64_t busy = (units + unit_total / longest_unit) / 2;
+  const int64_t unit_step = std::max<int64_t>(125, 80 + 90 * busy / cus);
   const int64_t unit_time = longest_unit * unit_step + 800;
   const int64_t bias = single_time > unit_time ? 95 : 100;
-  if (units <= cus && beside(unit_time, units, cus) * bias < 100 * std::min(whole_time, split_time))
+  if (units <= cus &&
+      beside(unit_time, units, cus, host) * bias < 100 * std::min(whole_time, split_time))
     return;
 
   // Pieces that read the same keys next to each other (by row, KV head and key range), the
