@@ -28,6 +28,7 @@ CASES = [
     ([2100], [2], 16, 1, 256, "tiles", 9),            # 32 rows, pieces of the minimum size
     ([4000, 17, 900], [51, 17, 40], 10, 2, 64, "tiles", 16),  # 255 rows; a prefill; short tiles
     ([2700, 300, 3064], [300, 1, 64], 14, 2, 256, "tiles", 12),  # a decode row beside chunk tiles
+    ([700, 3000, 64], [300, 1, 64], 14, 2, 64, "tiles", 1),   # where the host sets the time
     ([1700, 20000, 64], [300, 1, 64], 14, 2, 16, "units", 1),  # and one that fills the chip
     ([900], [850], 8, 8, 256, "tiles", 4),            # rows that see no key of the later splits
     ([6000], [10], 16, 1, 8, "tiles", 8),             # 16-head groups, few slots
